@@ -236,7 +236,8 @@ typedef struct {
     double mean_velocity[3];
     int tile_k;            /* variants 0, 1: z-planes per thread; 2: z-segment per block;
                               3, 5: block height in 64 x 4 tiles; 4, 6, 7: planes per block
-                              (2; 4 for variant 6 when pinned); 8: 2 */
+                              (2; 4 for variant 6 when pinned); 8: 2; 9: quantities
+                              per block; 10: 1 */
     int species_per_block; /* species per block chosen by the tile tuner */
     int kernel_variant;    /* 0: direct neighbour loads, 1: fields staged through LDS,
                               2: z-march with an LDS plane ring, 3: LDS-DMA copies (FP32),
@@ -247,7 +248,11 @@ typedef struct {
                               threads of a block (FP32; porous media), 8: gathered
                               chunks of up to 512 fluid nodes consecutive in a
                               tile-ordered compact storage, their halo copied
-                              by per-node lists (FP32; porous media). The
+                              by per-node lists (FP32; porous media), 9: one block
+                              per 256 nodes, species and quantity group, 10: each
+                              (species, quantity) field resident in one block for
+                              all steps of a call (at most 2,048 fluid nodes, 1,536
+                              in FP64). The
                               tuner times them in mp_init; the environment variable
                               LBMP_TILE = "variant,tile_k,species_per_block" pins one
                               (mp_init returns LBMP_EINVAL for a choice the lattice or

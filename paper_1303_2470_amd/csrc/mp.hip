@@ -81,6 +81,11 @@ struct GeomDev {
     const int32_t* gnode;
     const int32_t* gaslot;
     const uint16_t* gnbr;
+    // fluid nodes in lattice order: index of a lattice node (-1 on solid
+    // nodes) and back (variant 10)
+    const int32_t* fmap;       // [N]
+    const int32_t* fnode;      // [nf]
+    int nf;
     const T* coef;             // [S][4]
     const T* prob;             // [S][2] = p_a, p_d
     const double* kc;          // [S][KC]: p_a, p_d, c_0..c_3 (coef), -V_0..-V_2, FP64
@@ -1523,6 +1528,286 @@ __global__ void __launch_bounds__(NH * BLK) __attribute__((amdgpu_waves_per_eu(4
     finish(pend);
 }
 
+// ------------------------------------------------------------------ variants 9, 10
+// Launch-bound sizes. Variant 0 walks a block through its species and their
+// four quantities one after the other, each pass a round trip to the caches;
+// on a small lattice that chain is the whole step (64 species on a 32-node
+// slit: 226 us). The quantities of a species never meet within a step, so
+// both kernels below give every (species, quantity group) blocks of its own.
+// Arithmetic, its order and the rounding bits are those of variant 0 (FP64
+// chain over the links in order), so the fields are bitwise the same; block
+// sums group nodes differently and agree to rounding.
+
+// Lane 31 of the wave broadcast to rows 2 and 3; rows 0 and 1 receive 0.
+__device__ __forceinline__ double dpp_bcast31(double v) {
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, 0x143, 0xC, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), 0x143, 0xC, 0xF, false);
+    return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
+}
+// Sum over the 64 lanes in a fixed order, in lane 63.
+__device__ __forceinline__ double wave_sum(double v) {
+    v += dpp_f64<0xB1>(v);    // quad_perm [1,0,3,2]
+    v += dpp_f64<0x4E>(v);    // quad_perm [2,3,0,1]
+    v += dpp_f64<0x124>(v);   // row_ror:4
+    v += dpp_f64<0x128>(v);   // row_ror:8
+    v += dpp_bcast15(v);
+    v += dpp_bcast31(v);
+    return v;
+}
+// The two series slots of quantity q: density in 3 (mobile) and 7 (adsorbed);
+// first moment q in q - 1 (VACF term) and 3 + q (total, mobile and adsorbed).
+__device__ __forceinline__ int sum_slot(int q, int j) { return j == 0 ? (q == 0 ? 3 : q - 1) : (q == 0 ? 7 : 3 + q); }
+
+// Variant 9: one block per 256 lattice nodes, species and group of QB
+// quantities (dense fields). All 18 QB neighbour loads of a node are in
+// flight together; more blocks (QB = 1) where the lattice leaves CUs idle,
+// fewer reads of the link table (QB = 4) where it does not. nqb = 4 / QB
+// groups, or 1 in uptake mode, where only the density moves. Bound by the
+// chain of dependent loads (node class, interface slot, adsorbed value).
+// 40^3 fcc cell, 3 species, FP64 uptake: 24.5 us a step with variant 0, 10.1
+// with this.
+template <typename T, int QB>
+__global__ void __launch_bounds__(BLK) k_mp_flat(const GeomDev<T>* __restrict__ geoms, int ngeom, int nqb,
+                                                 int64_t nblocks, const Ctl* __restrict__ ctl) {
+    __shared__ double wsum[BLK / 64][2 * QB];
+    constexpr int E = (int)sizeof(T);
+    T* const tag = nullptr;
+    double* const dtag = nullptr;
+    const int64_t lb = xcd_remap(blockIdx.x, nblocks);
+    const int gi = find_geom(geoms, ngeom, lb);
+    const GeomDev<T>& G = geoms[gi];
+    const uint32_t local = (uint32_t)(lb - G.blk0), per = (uint32_t)(G.S * nqb);
+    const uint32_t tile = local / per, sq = local - tile * per;
+    const int s = (int)(sq / nqb), q0 = (int)(sq % nqb) * QB;
+    const uint32_t nx = G.nx, ny = G.ny, nz = G.nz, plane = nx * ny;
+    const int N = (int)G.N;
+    const uint32_t n = tile * BLK + threadIdx.x;
+    const bool in = n < (uint32_t)N;
+    const bool act = in && G.cls[in ? n : 0] != 0;
+    const int64_t ntile = G.ntile;
+    double* const part = G.part + ((int64_t)s * ntile + tile) * NRED;
+    const bool only_q0 = QB == 1 && nqb == 1;
+    if (!__syncthreads_or(act)) {  // no fluid node: zero sums
+        if (threadIdx.x < 2 * QB) part[sum_slot(q0 + threadIdx.x / 2, threadIdx.x & 1)] = 0.0;
+        if (only_q0 && threadIdx.x < NRED) part[threadIdx.x] = 0.0;
+        return;
+    }
+    const uint32_t m = act ? n : 0, z = m / plane, r2 = m - z * plane, y = r2 / nx, x = r2 - y * nx;
+    const uint32_t xo[3] = {x == 0 ? nx - 1 : x - 1, x, x + 1 == nx ? 0 : x + 1};
+    const uint32_t yo[3] = {(y == 0 ? ny - 1 : y - 1) * nx, y * nx, (y + 1 == ny ? 0 : y + 1) * nx};
+    const uint32_t zo[3] = {(z == 0 ? nz - 1 : z - 1) * plane, z * plane, (z + 1 == nz ? 0 : z + 1) * plane};
+    const int offn = act ? (int)n * E : OOB;
+    int off[NL];  // source r - c_k of link k
+#pragma unroll
+    for (int k = 0; k < NL; ++k)
+        off[k] = act ? (int)(zo[1 - lcz(k)] + yo[1 - lcy(k)] + xo[1 - lcx(k)]) * E : OOB;
+    const int64_t t = ctl->t;
+    const T* const Xin = (t & 1) ? G.X1 : G.X0;
+    T* const Xout = (t & 1) ? G.X0 : G.X1;
+    const int sl = act ? G.slot[n] : -1;
+    const bool isI = sl >= 0;
+    const int offa = isI ? sl * E : OOB;
+    const int64_t NI = G.NI;
+    T v[QB][NL], xc[QB], xa[QB], pin[NL], av[QB];
+#pragma unroll
+    for (int j = 0; j < QB; ++j) {
+        const int64_t f = 4 * s + q0 + j;
+        const auto rin = mkrsrc(Xin + f * N, (int64_t)N * E);
+        xc[j] = bload(tag, rin, offn);
+#pragma unroll
+        for (int k = 0; k < NL; ++k) v[j][k] = bload(tag, rin, off[k]);
+        xa[j] = bload(tag, mkrsrc(G.Xa + f * NI, NI * E), offa);
+    }
+#pragma unroll
+    for (int k = 0; k < NL; ++k) pin[k] = bload(tag, mkrsrc(G.pin + (int64_t)k * N, (int64_t)N * E), offn);
+    const double sig = bload(dtag, mkrsrc(G.sig, (int64_t)N * 8), act ? (int)n * 8 : OOB);
+    const double src = (double)bload(tag, mkrsrc(G.src, (int64_t)N * E), offn);
+#pragma unroll
+    for (int j = 0; j < QB; ++j)
+        av[j] = q0 + j > 0 ? bload(tag, mkrsrc(G.a + (int64_t)(q0 + j - 1) * N, (int64_t)N * E), offn) : T(0);
+    const double pa = (double)G.prob[2 * s], pd = (double)G.prob[2 * s + 1];
+    const uint32_t rbase = hash32((act ? n : 0u) * 0x9e3779b9u ^ hash32((uint32_t)t ^ ((uint32_t)gi << 24)));
+    uint32_t rs = hash32(rbase ^ ((uint32_t)s * 0x632be5abu)) | 1u;
+    for (int j = 0; j < q0; ++j) (void)xorshift32(rs);  // one draw per quantity
+    double red[2 * QB];
+#pragma unroll
+    for (int j = 0; j < QB; ++j) {
+        const int q = q0 + j;
+        const int64_t f = 4 * s + q;
+        double acc = 0.0;  // arrivals (Eq. 7)
+#pragma unroll
+        for (int k = 0; k < NL; ++k) acc = __builtin_fma((double)v[j][k], (double)pin[k], acc);
+        const double c = (double)xc[j], a = (double)xa[j];
+        const double fa = isI ? pa * c : 0.0;   // adsorption (Eq. 9)
+        const double fd = pd * a;               // desorption (Eq. 10); a = 0 off the interface
+        double nv = __builtin_fma(-c, sig, c);  // the part that stays (Eq. 7)
+        nv = __builtin_fma((double)G.coef[f], src, (nv - fa) + fd) + acc;
+        const uint32_t r1 = xorshift32(rs);
+        bstore(store_round<T>(nv, r1), mkrsrc(Xout + f * N, (int64_t)N * E), offn);
+        bstore(store_round<T>((a + fa) - fd, (r1 >> 3) | (r1 << 29)), mkrsrc(G.Xa + f * NI, NI * E), offa);
+        red[2 * j] = q == 0 ? c : c * (double)av[j];
+        red[2 * j + 1] = q == 0 ? a : c + a;
+    }
+#pragma unroll
+    for (int j = 0; j < 2 * QB; ++j) red[j] = wave_sum(red[j]);
+    if ((threadIdx.x & 63) == 63)
+#pragma unroll
+        for (int j = 0; j < 2 * QB; ++j) wsum[threadIdx.x >> 6][j] = red[j];
+    __syncthreads();
+    if (only_q0 && threadIdx.x < NRED && threadIdx.x != 3 && threadIdx.x != 7) part[threadIdx.x] = 0.0;
+    if (threadIdx.x < 2 * QB) {
+        const int j = threadIdx.x;
+        part[sum_slot(q0 + j / 2, j & 1)] = ((wsum[0][j] + wsum[1][j]) + wsum[2][j]) + wsum[3][j];
+    }
+}
+
+// Variant 10: lattices of at most 2,048 (FP32) or 1,536 (FP64) fluid nodes. One block owns a whole
+// (geometry, species, quantity) field and runs all steps of the call in one
+// launch: the field lives in two LDS buffers (fluid nodes only), the link
+// table, the arrival positions and the adsorbed values in registers (NPT
+// nodes per thread), and a step is 18 LDS reads per node, one barrier and the
+// two sums, whose last stage runs while the next step does. No traffic leaves
+// the CU but the sums. Bound by the latency of a step's LDS reads and of the
+// chain of 18 FP64 FMAs behind them: 0.7 us a step for 64 species on a 32-node
+// slit (231 us with variant 0's launch per step). The node limit is what the
+// registers of a CU hold.
+constexpr int res_npt(int prec) { return prec == LBMP_FP32 ? 4 : 3; }  // nodes per thread of the 512-thread block
+constexpr int RES_CHUNK = 4096;  // steps per launch
+
+template <typename T, int BS, int NPT>
+__global__ void __launch_bounds__(BS) k_mp_resident(const GeomDev<T>* __restrict__ geoms, int ngeom, int nq,
+                                                    int nsteps, Ctl* ctl) {
+    constexpr int NW = BS / 64, ZS = BS * NPT;  // ZS: the slot of links from solid nodes, always zero
+    __shared__ T xs[2][ZS + 1];
+    __shared__ double ws[2][NW][2];
+    const int gi = find_geom(geoms, ngeom, (int64_t)blockIdx.x);
+    const GeomDev<T>& G = geoms[gi];
+    const int local = (int)(blockIdx.x - G.blk0);
+    const int s = local / nq, q = local - s * nq;
+    const int nx = G.nx, ny = G.ny, nz = G.nz, nf = G.nf;
+    const int64_t N = G.N, NI = G.NI, f = 4 * s + q;
+    const int tid = threadIdx.x;
+    const int64_t t0 = ctl->t, tmax = ctl->tmax;
+    const double mass_ref = ctl->mass_ref, drift_max = ctl->drift_max;
+    const T* const Xin = ((t0 & 1) ? G.X1 : G.X0) + f * N;
+    T* const Xa = G.Xa + f * NI;
+    T pin[NPT][NL];
+    uint32_t nb[NPT][NL / 2];  // arrival slots, two per register
+    double sig[NPT], src[NPT], av[NPT];
+    uint32_t hn[NPT];
+    T xa[NPT];
+    int sl[NPT];
+#pragma unroll
+    for (int j = 0; j < NPT; ++j) {
+        const int i = tid + j * BS;
+        const bool act = i < nf;
+        const int n = act ? G.fnode[i] : 0;
+        const int z = n / (nx * ny), r2 = n - z * nx * ny, y = r2 / nx, x = r2 - y * nx;
+#pragma unroll
+        for (int k = 0; k < NL; ++k) {
+            const int64_t m = (int64_t)wrapi(x - lcx(k), nx) +
+                              (int64_t)nx * (wrapi(y - lcy(k), ny) + (int64_t)ny * wrapi(z - lcz(k), nz));
+            const int32_t c = act ? G.fmap[m] : -1;
+            const uint32_t slot = c < 0 ? (uint32_t)ZS : (uint32_t)c;
+            if (k & 1) nb[j][k / 2] |= slot << 16; else nb[j][k / 2] = slot;
+            pin[j][k] = act ? G.pin[(int64_t)k * N + n] : T(0);
+        }
+        sig[j] = act ? G.sig[n] : 0.0;
+        src[j] = act ? (double)G.src[n] : 0.0;
+        av[j] = act && q > 0 ? (double)G.a[(int64_t)(q - 1) * N + n] : 0.0;
+        sl[j] = act ? G.slot[n] : -1;
+        xa[j] = sl[j] >= 0 ? Xa[sl[j]] : T(0);
+        hn[j] = (uint32_t)n * 0x9e3779b9u;
+        xs[0][i] = act ? Xin[n] : T(0);
+        xs[1][i] = T(0);
+    }
+    if (tid < 2) xs[tid][ZS] = T(0);
+    const double pa = (double)G.prob[2 * s], pd = (double)G.prob[2 * s + 1], cq = (double)G.coef[f];
+    double* const series = G.series + (int64_t)s * NRED;
+    const int64_t stride = (int64_t)G.S * NRED;
+    // sums of step it (time t0 + it), once every wave's part is in ws[it & 1]
+    auto record = [&](int it) {
+        const int64_t t = t0 + it;
+        if (tid < 2 && t <= tmax) {
+            double r = ws[it & 1][0][tid];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) r += ws[it & 1][w][tid];
+            series[(t - 1) * stride + sum_slot(q, tid)] = r;
+            const double other = dpp_f64<0xB1>(r);  // lanes 0 and 1 swap sums
+            if (q == 0 && tid == 0 && !(fabs(r + other - mass_ref) <= drift_max))
+                atomicMin(reinterpret_cast<unsigned long long*>(&ctl->bad_t), (unsigned long long)t);
+        }
+        if (nq == 1 && tid < NRED && tid != 3 && tid != 7 && t <= tmax) series[(t - 1) * stride + tid] = 0.0;
+    };
+    for (int it = 0; it < nsteps; ++it) {
+        __syncthreads();  // the field of this step and the sums of the last one are complete
+        if (it > 0 && tid < 64) record(it - 1);
+        const T* const cur = xs[it & 1];
+        T* const nxt = xs[(it & 1) ^ 1];
+        const uint32_t ht = hash32((uint32_t)(t0 + it) ^ ((uint32_t)gi << 24));
+        double r0 = 0.0, r1 = 0.0;
+#pragma unroll
+        for (int j = 0; j < NPT; ++j) {
+            const int i = tid + j * BS;
+            double acc = 0.0;  // arrivals (Eq. 7)
+            // several nodes per thread: what is derived from the packed slots and
+            // the table is formed anew each step (hoisted, it would not fit)
+            if constexpr (NPT > 1) {
+#pragma unroll
+                for (int k = 0; k < NL / 2; ++k) asm volatile("" : "+v"(nb[j][k]));
+                if constexpr (std::is_same<T, float>::value)
+#pragma unroll
+                    for (int k = 0; k < NL; ++k) asm volatile("" : "+v"(pin[j][k]));
+            }
+#pragma unroll
+            for (int k = 0; k < NL; ++k) {
+                const uint32_t slot = (k & 1) ? nb[j][k / 2] >> 16 : nb[j][k / 2] & 0xffffu;
+                acc = __builtin_fma((double)cur[slot], (double)pin[j][k], acc);
+            }
+            const double c = (double)cur[i], a = (double)xa[j];
+            const double fa = sl[j] >= 0 ? pa * c : 0.0;  // adsorption (Eq. 9)
+            const double fd = pd * a;                     // desorption (Eq. 10)
+            double nv = __builtin_fma(-c, sig[j], c);     // the part that stays (Eq. 7)
+            nv = __builtin_fma(cq, src[j], (nv - fa) + fd) + acc;
+            uint32_t rs = 0;
+            if constexpr (std::is_same<T, float>::value) {
+                rs = hash32(hash32(hn[j] ^ ht) ^ ((uint32_t)s * 0x632be5abu)) | 1u;
+                for (int d = 0; d < q; ++d) (void)xorshift32(rs);  // one draw per quantity
+                rs = xorshift32(rs);
+            }
+            nxt[i] = i < nf ? store_round<T>(nv, rs) : T(0);
+            xa[j] = sl[j] >= 0 ? store_round<T>((a + fa) - fd, (rs >> 3) | (rs << 29)) : T(0);
+            r0 += q == 0 ? c : c * av[j];
+            r1 += q == 0 ? a : c + a;
+            if constexpr (NPT > 1) __builtin_amdgcn_sched_barrier(0);  // one node's reads in flight at a time
+        }
+        r0 = wave_sum(r0);
+        r1 = wave_sum(r1);
+        if ((tid & 63) == 63) {
+            ws[it & 1][tid >> 6][0] = r0;
+            ws[it & 1][tid >> 6][1] = r1;
+        }
+    }
+    __syncthreads();
+    if (nsteps > 0 && tid < 64) record(nsteps - 1);
+    T* const Xout = (((t0 + nsteps) & 1) ? G.X1 : G.X0) + f * N;
+#pragma unroll
+    for (int j = 0; j < NPT; ++j) {
+        const int i = tid + j * BS;
+        if (i < nf) Xout[G.fnode[i]] = xs[nsteps & 1][i];
+        if (sl[j] >= 0) Xa[sl[j]] = xa[j];
+    }
+    // the last block to finish moves the state time on (every block has read it)
+    if (tid == 0) {
+        __threadfence();
+        if (atomicAdd(&ctl->done, 1u) == gridDim.x - 1) {
+            ctl->done = 0;
+            ctl->t = t0 + nsteps;
+        }
+    }
+}
+
 // Lattices with many tiles: chunks of RCH tile partials of every
 // (geometry, species) summed by one block each, in a fixed order, into
 // chunk[work][chunk][NRED]; k_mp_reduce then adds the chunks.
@@ -1851,6 +2136,7 @@ struct GeomHost {
     void *pin, *sig, *src, *a, *X0, *X1, *Xa, *coef, *prob;
     double *part, *series, *spc, *spc0, *kc, *zout, *dout;
     int32_t* fidx;  // [N] index of a fluid node among the fluid nodes in lattice order, -1 on solid
+    int32_t* fnode; // [nf] lattice index of a fluid node
     std::vector<int32_t> fidx_h;  // host copy
     // gathered chunks (variant 8): the compact order of their fields (gidx,
     // tiles of 32 x 4 x 4 nodes), chunk table, halo quads, neighbour slots, lattice
@@ -1880,7 +2166,9 @@ struct lbmp_mp {
     double* chunk;   // [nwork][nch_max][NRED] chunk sums of the series reduction
     int nch_max, nch;
     double* setup_tmp;
-    int K, gsz, variant;  // variant 0: direct loads, 1: LDS-staged box, 2: z-march, 3-7: LDS DMA, 8: gathered chunks (FP32)
+    // variant 0: direct loads, 1: LDS-staged box, 2: z-march, 3-7: LDS DMA, 8: gathered chunks (FP32),
+    // 9: one block per tile, species and quantity group, 10: fields resident in LDS
+    int K, gsz, variant;
     int uptake;           // out-of-equilibrium density propagation (no VACF)
     int64_t nblocks;
     hipGraph_t graph = nullptr;
@@ -1907,6 +2195,8 @@ int64_t ntile_for(const lbmp_flow* f, int K, int variant) {
         return K * (int64_t)((f->nx + TX - 1) / TX) * ((f->ny + K * TY - 1) / (K * TY)) * f->nz;
     // variant 4 (6: full rows, 7: lane compaction): K reduction tiles (TX x TY) per block of K planes
     if (variant == 4 || variant == 6 || variant == 7) return K * (int64_t)((f->nx + TX - 1) / TX) * ((f->ny + TY - 1) / TY) * ((f->nz + K - 1) / K);
+    if (variant == 9) return (f->N + BLK - 1) / BLK;
+    if (variant == 10) return 1;
     if (variant >= 1) return (int64_t)((f->nx + TX - 1) / TX) * ((f->ny + TY - 1) / TY) * zb;
     return (((int64_t)f->nx * f->ny + BLK - 1) / BLK) * zb;
 }
@@ -1929,6 +2219,7 @@ void carve_geom(GeomHost& g, Carver& c, int64_t tmax) {
     g.X1 = c.take<T>(S * 4 * N);
     g.Xa = c.take<T>(S * 4 * NIa);
     g.fidx = c.take<int32_t>(N);
+    g.fnode = c.take<int32_t>(std::max<int64_t>(g.nf, 1));
     {
         const int64_t NF = std::max<int64_t>(g.nf, 1), nch = gather_chunk_cap(NF);
         g.gidx = c.take<int32_t>(N);
@@ -2024,10 +2315,47 @@ lbmp_mp* make_handle(const lbmp_flow* const* flows, const lbmp_species* species,
     return h;
 }
 
+// quantities a step moves: in uptake mode the first moments are zero and stay zero
+int nquant(const lbmp_mp* h) { return h->uptake ? 1 : 4; }
+int max_nf(const lbmp_mp* h) {
+    int64_t m = 0;
+    for (const auto& g : h->g) m = std::max(m, g.nf);
+    return (int)m;
+}
+
+// n steps of the resident kernel in one launch, threads and nodes per thread
+// by the largest geometry: one node per thread up to 1,024 (more waves hide
+// the LDS latency of each other's chains), then several per thread in 512.
+template <typename T>
+void launch_resident(lbmp_mp* h, int n, hipStream_t s) {
+    auto* G = static_cast<const GeomDev<T>*>(h->geoms_dev);
+    const unsigned grid = (unsigned)h->nblocks;
+    const int m = max_nf(h), nq = nquant(h);
+    if (m <= 64) k_mp_resident<T, 64, 1><<<grid, 64, 0, s>>>(G, h->ngeom, nq, n, h->ctl);
+    else if (m <= 128) k_mp_resident<T, 128, 1><<<grid, 128, 0, s>>>(G, h->ngeom, nq, n, h->ctl);
+    else if (m <= 256) k_mp_resident<T, 256, 1><<<grid, 256, 0, s>>>(G, h->ngeom, nq, n, h->ctl);
+    else if (m <= 512) k_mp_resident<T, 512, 1><<<grid, 512, 0, s>>>(G, h->ngeom, nq, n, h->ctl);
+    else if (m <= 1024) k_mp_resident<T, 1024, 1><<<grid, 1024, 0, s>>>(G, h->ngeom, nq, n, h->ctl);
+    else k_mp_resident<T, 512, res_npt(8 * sizeof(T))><<<grid, 512, 0, s>>>(G, h->ngeom, nq, n, h->ctl);
+}
+
 template <typename T>
 void launch_step_kernel(lbmp_mp* h, hipStream_t s) {
     auto* G = static_cast<const GeomDev<T>*>(h->geoms_dev);
     dim3 grid((unsigned)h->nblocks);
+    if (h->variant == 10) {
+        launch_resident<T>(h, 1, s);
+        return;
+    }
+    if (h->variant == 9) {
+        const int nqb = nquant(h) / h->K;
+        switch (h->K) {
+            case 1: k_mp_flat<T, 1><<<grid, BLK, 0, s>>>(G, h->ngeom, nqb, h->nblocks, h->ctl); break;
+            case 2: k_mp_flat<T, 2><<<grid, BLK, 0, s>>>(G, h->ngeom, nqb, h->nblocks, h->ctl); break;
+            default: k_mp_flat<T, 4><<<grid, BLK, 0, s>>>(G, h->ngeom, nqb, h->nblocks, h->ctl); break;
+        }
+        return;
+    }
     if (h->variant >= 3) {
         if constexpr (std::is_same<T, float>::value) {
             if (h->variant == 4) k_mp_dma<2, true, false><<<grid, 2 * BLK, 0, s>>>(G, h->ngeom, h->gsz, h->nblocks, h->ctl);
@@ -2063,6 +2391,7 @@ void launch_step_kernel(lbmp_mp* h, hipStream_t s) {
 
 template <typename T>
 void launch_step_tail(lbmp_mp* h, hipStream_t s) {
+    if (h->variant == 10) return;  // the kernel records its sums and moves the time itself
     auto* G = static_cast<const GeomDev<T>*>(h->geoms_dev);
     if (h->nch > 1)
         k_mp_reduce_chunks<T><<<(unsigned)(h->nwork * h->nch), BLK, 0, s>>>(G, h->work, h->nch, h->chunk);
@@ -2077,6 +2406,13 @@ void launch_step(lbmp_mp* h, hipStream_t s) {
 }
 
 void do_steps(lbmp_mp* h, int64_t n, hipStream_t s) {
+    if (h->variant == 10) {
+        for (; n > 0; n -= RES_CHUNK) {
+            const int m = (int)std::min<int64_t>(n, RES_CHUNK);
+            if (h->prec == LBMP_FP32) launch_resident<float>(h, m, s); else launch_resident<double>(h, m, s);
+        }
+        return;
+    }
     for (int64_t i = 0; i < n; ++i) {
         if (h->prec == LBMP_FP32) launch_step<float>(h, s); else launch_step<double>(h, s);
     }
@@ -2108,16 +2444,17 @@ lbmp_status upload_geoms(lbmp_mp* h) {
         d.N = g.N; d.NI = std::max<int64_t>(g.NI, 1);
         d.pb = (int)(((int64_t)f->nx * f->ny + BLK - 1) / BLK);
         d.zb = (f->nz + h->K - 1) / h->K;
-        d.ngrp = (g.S + h->gsz - 1) / h->gsz;
+        d.ngrp = h->variant >= 9 ? g.S * (nquant(h) / h->K) : (g.S + h->gsz - 1) / h->gsz;
         d.ntile = h->variant == 8 ? g.gnh * g.nch : ntile_for(f, h->K, h->variant);
         d.blk0 = blk;
         // variants 3-7: one block per K tiles; variant 8: one per chunk
-        blk += (h->variant == 8 ? g.nch : (h->variant >= 3 ? d.ntile / h->K : d.ntile)) * d.ngrp;
+        blk += (h->variant == 8 ? g.nch : (h->variant >= 3 && h->variant < 8 ? d.ntile / h->K : d.ntile)) * d.ngrp;
         d.cls = f->d.cls; d.slot = f->d.slot;
         d.pin = (const T*)g.pin; d.sig = (const double*)g.sig; d.src = (const T*)g.src; d.a = (const T*)g.a;
         d.X0 = (T*)g.X0; d.X1 = (T*)g.X1; d.Xa = (T*)g.Xa;
         d.fidx = cidx(h, g);
         d.gch = g.gch; d.ghsrc = g.ghsrc; d.gnode = g.gnode; d.gaslot = g.gaslot; d.gnbr = g.gnbr;
+        d.fmap = g.fidx; d.fnode = g.fnode; d.nf = (int)g.nf;
         d.NC = compact_fields(h) ? g.nf : g.N;
         d.coef = (const T*)g.coef; d.prob = (const T*)g.prob;
         d.kc = g.kc;
@@ -2230,7 +2567,12 @@ bool tile_allowed(const lbmp_mp* h, int v, int K, int gs) {
                       ((v == 5 || v == 6) && K == 2 && full_rows(h)) || (v == 6 && K == 4 && full_rows(h)) ||
                       (v == 8 && K == 2 && gather)) &&
                      gs >= 1 && gs <= DMA_GMAX && h->prec == LBMP_FP32 && dma_fits(h);
-    return ok01 || ok2 || ok3;
+    // variant 9: blocks of 256 nodes x species x groups must stay a 32-bit count
+    bool flat = true;
+    for (const auto& g : h->g) flat = flat && (g.N + BLK - 1) / BLK * g.S * 4 <= (int64_t)INT32_MAX;
+    const bool ok9 = v == 9 && gs == 1 && flat && (h->uptake ? K == 1 : (K == 1 || K == 2 || K == 4));
+    const bool ok10 = v == 10 && K == 1 && gs == 1 && max_nf(h) <= 512 * res_npt(h->prec);
+    return ok01 || ok2 || ok3 || ok9 || ok10;
 }
 
 // Pick (K, species per block) by timing steps of each candidate on the
@@ -2262,7 +2604,9 @@ lbmp_status autotune(lbmp_mp* h) {
                                  "(FP32 only) with K = 1 or 2 (block height in 64 x 4 tiles), or variant 4 (FP32 only) with K = 2 "
                                  "(z-planes per block), or variants 5, 6 (variants 3, 4 with full rows: FP32, nx = 64 in every "
                                  "geometry) with K = 2, or variant 7 (variant 4 with lane compaction, FP32) with K = 2, "
-                                 "or variant 8 (gathered chunks, FP32) with K = 2; at most 64 species per block for 3-8");
+                                 "or variant 8 (gathered chunks, FP32) with K = 2; at most 64 species per block for 3-8; "
+                                 "or variant 9 with K = 1, 2 or 4 quantities per block (1 for uptake) and 1 species, or "
+                                 "variant 10 with K = 1 and 1 species (at most 2,048 fluid nodes in every geometry, 1,536 in FP64)");
     }
     auto it = g_tune_cache.find(key);
     if (it != g_tune_cache.end()) {
@@ -2282,10 +2626,14 @@ lbmp_status autotune(lbmp_mp* h) {
             return upload(h);
         }
     }
-    if (work < (1 << 16)) {  // launch-bound sizes: one block per tile, all species
+    // Launch-bound sizes, where timing candidates would cost more than any of
+    // them could save: the resident kernel wherever the fields fit its blocks
+    // (0.7 against 12 us a step on a 32-node slit), else one quantity per block
+    // (12 against 21-26 us a step for variant 0 on 17 k nodes x 3 species).
+    if (work < (1 << 16)) {
+        h->gsz = 1;
         h->K = 1;
-        h->gsz = maxS;
-        h->variant = 0;
+        h->variant = tile_allowed(h, 10, 1, 1) ? 10 : 9;
         g_tune_cache[key] = {h->K, h->gsz, h->variant};
         return upload(h);
     }
@@ -2294,6 +2642,9 @@ lbmp_status autotune(lbmp_mp* h) {
         for (int K : {1, 2})
             for (int gs : {1, 2, 4, 8, 16, 32, 64})
                 if (gs <= maxS || gs == 1) cand.push_back({K, gs, v});
+    for (int K : {1, 2, 4})
+        if (tile_allowed(h, 9, K, 1)) cand.push_back({K, 1, 9});
+    if (tile_allowed(h, 10, 1, 1)) cand.push_back({1, 1, 10});
     int maxz = 0;
     for (auto& g : h->g) maxz = std::max(maxz, g.flow->nz);
     for (int zs : {8, 16, 32, 64})
@@ -2502,12 +2853,17 @@ lbmp_status build_fidx(GeomHost& g, hipStream_t s) {
     std::vector<int8_t> cls(g.N);
     LBMP_HIP(hipMemcpyAsync(cls.data(), g.flow->d.cls, g.N, hipMemcpyDeviceToHost, s));
     LBMP_HIP(hipStreamSynchronize(s));
-    std::vector<int32_t> fi(g.N);
-    int64_t c = 0;
-    for (int64_t n = 0; n < g.N; ++n) fi[n] = cls[n] ? (int32_t)c++ : -1;
+    std::vector<int32_t> fi(g.N), fn;
+    fn.reserve(g.nf);
+    for (int64_t n = 0; n < g.N; ++n) {
+        fi[n] = cls[n] ? (int32_t)fn.size() : -1;
+        if (cls[n]) fn.push_back((int32_t)n);
+    }
+    const int64_t c = (int64_t)fn.size();
     if (c != g.nf) return fail(LBMP_ESTATE, "fluid node count %lld differs from the flow's %lld", (long long)c,
                                (long long)g.nf);
     LBMP_HIP(hipMemcpyAsync(g.fidx, fi.data(), g.N * 4, hipMemcpyHostToDevice, s));
+    LBMP_HIP(hipMemcpyAsync(g.fnode, fn.data(), g.nf * 4, hipMemcpyHostToDevice, s));
     LBMP_HIP(hipStreamSynchronize(s));
     g.fidx_h = std::move(fi);
     return LBMP_OK;
@@ -2899,7 +3255,7 @@ extern "C" lbmp_status mp_step_n(lbmp_mp* h, int64_t n_steps) {
     hipStream_t s = h->stream;
     int64_t left = n_steps;
     // replay a captured chunk of steps when the stream can be captured
-    if (s != nullptr && left >= 2 * GRAPH_CHUNK) {
+    if (s != nullptr && left >= 2 * GRAPH_CHUNK && h->variant != 10) {
         if (!h->gexec) {
             LBMP_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
             do_steps(h, GRAPH_CHUNK, s);
