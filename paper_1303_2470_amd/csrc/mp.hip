@@ -2077,32 +2077,104 @@ __global__ void k_init_uptake(const int8_t* __restrict__ cls, int64_t N, double 
         X[(int64_t)(4 * s) * NC + (fidx ? fidx[n] : n)] = cls[n] != 0 ? (T)rho0 : T(0);
 }
 
-// Time series of Z_g and D_g (discrete Eq. 3 about the mean drift) for one
-// geometry, one thread per (species, direction), compensated summation.
+// Sum of two double-doubles (hi + lo with |lo| at most half an ulp of hi).
+struct DD {
+    double hi, lo;
+};
+__device__ __forceinline__ DD dd_add(DD a, DD b) {
+    const double s = a.hi + b.hi, bb = s - a.hi;
+    const double e = ((a.hi - (s - bb)) + (b.hi - bb)) + (a.lo + b.lo);
+    const double hi = s + e;
+    return {hi, e - (hi - s)};
+}
+
+// Times t0 .. t0 + count - 1 of Z_g and D_g (discrete Eq. 3 about the mean
+// drift) for one geometry, [species][direction][count], one block per species
+// and direction.
 // Z(t) = V^2 + sum_r dP a - E(t) V, where E(t) = sum dP + sum dP_ads is the
 // total of the first-moment deviations (zero in exact arithmetic; the term
-// removes the rounding drift of the stored total from the VACF).
-__global__ void k_vacf_series(const double* __restrict__ series, int S, int64_t T, int64_t stride,
-                              const double* __restrict__ spc0, double* __restrict__ Zo,
-                              double* __restrict__ Do) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= 3 * S) return;
-    const int s = i / 3, g = i % 3;
+// removes the rounding drift of the stored total from the VACF). D is a prefix
+// sum over all times up to the window's end: a scan in double-double (error
+// far below one rounding of the result) over VSC times at once, the carry
+// passing from one stretch to the next. Bound by the latency of a stretch's
+// loads and scan; one thread per series, adding time after time, took 232 us
+// for 1,000 times. The window goes out as one contiguous block: with rows
+// spaced by all recordable times each row was a copy of its own (a call for
+// 301 times of 64 species: 3.2 ms, now 0.1 ms).
+// tail: mobile and adsorbed total of every species at the last step (zeros
+// before the first), then the watchdog's first bad time as an integer.
+constexpr int VSC = 512;
+
+__global__ void __launch_bounds__(VSC) k_vacf_series(const double* __restrict__ series, int S, int64_t T, int64_t t0,
+                                                     int64_t count, const double* __restrict__ spc0,
+                                                     const Ctl* __restrict__ ctl, double* __restrict__ Zo,
+                                                     double* __restrict__ Do, double* __restrict__ tail) {
+    constexpr int NW = VSC / 64;
+    __shared__ DD wtot[2][NW];
+    const int s = blockIdx.x, g = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const double V = spc0[4 * s + g];
     const double z0 = spc0[(int64_t)S * 4 + 3 * s + g];
-    double* Z = Zo + (int64_t)i * stride;
-    double* D = Do + (int64_t)i * stride;
-    Z[0] = z0;
-    double sum = 0.5 * (z0 - V * V), comp = 0.0;
-    D[0] = sum;
-    for (int64_t t = 1; t <= T; ++t) {
-        const double* e = series + ((t - 1) * S + s) * NRED;
-        const double c = e[g] - e[4 + g] * V;
-        Z[t] = V * V + c;
-        const double tt = sum + c;
-        comp += fabs(sum) >= fabs(c) ? (sum - tt) + c : (c - tt) + sum;
-        sum = tt;
-        D[t] = sum + comp;
+    if (g == 0 && tid < 2) tail[2 * s + tid] = T > 0 ? series[((T - 1) * S + s) * NRED + (tid == 0 ? 3 : 7)] : 0.0;
+    if (g == 0 && s == 0 && tid == 0) reinterpret_cast<int64_t*>(tail)[2 * S] = ctl->bad_t;
+    double* const Z = Zo + (int64_t)(3 * s + g) * count - t0;
+    double* const D = Do + (int64_t)(3 * s + g) * count - t0;
+    DD carry{0.5 * (z0 - V * V), 0.0};
+    if (tid == 0 && t0 == 0 && count > 0) {
+        Z[0] = z0;
+        D[0] = carry.hi;
+    }
+    const int64_t end = t0 + count - 1;
+    int par = 0;
+    for (int64_t base = 1; base <= end; base += VSC, par ^= 1) {
+        const int64_t t = base + tid;
+        double c = 0.0;
+        if (t <= end) {
+            const double* e = series + ((t - 1) * S + s) * NRED;
+            c = e[g] - e[4 + g] * V;
+        }
+        DD v{c, 0.0};
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const DD u{__shfl_up(v.hi, off, 64), __shfl_up(v.lo, off, 64)};
+            if (lane >= off) v = dd_add(u, v);
+        }
+        if (lane == 63) wtot[par][wv] = v;
+        __syncthreads();  // the other buffer's readers are past the barrier before this one
+        DD pre = carry;
+        for (int w = 0; w < NW; ++w) {
+            if (w == wv) v = dd_add(pre, v);
+            pre = dd_add(pre, wtot[par][w]);
+        }
+        carry = pre;
+        if (t >= t0 && t <= end) {
+            Z[t] = V * V + c;
+            D[t] = v.hi + v.lo;
+        }
+    }
+}
+
+// The current state of one species in FP64 on the dense lattice: stored
+// deviations plus their reference c_q rho_ref w (mobile, fluid nodes) and
+// c_q Gamma_ref w (adsorbed, interfacial nodes), zero elsewhere. fidx: compact
+// index of a node (null: dense fields), aperm: adsorbed-field index of an
+// interface slot (null: the slot itself), w: relative Eq. 11 weight (null: 1).
+template <typename T>
+__global__ void k_state_out(const int8_t* __restrict__ cls, const int32_t* __restrict__ slot, int64_t N, int64_t NC,
+                            int64_t NI, const int32_t* __restrict__ fidx, const int32_t* __restrict__ aperm,
+                            const double* __restrict__ w, const T* __restrict__ X, const T* __restrict__ Xa, double4 cr,
+                            double4 cg, double* __restrict__ Xo, double* __restrict__ Xao) {
+    const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (n >= N) return;
+    const bool fl = cls[n] != 0;
+    const int64_t i = fl && fidx ? fidx[n] : n;
+    const int32_t sl = fl ? slot[n] : -1;
+    const int64_t ia = sl >= 0 && aperm ? aperm[sl] : sl;
+    const double wn = w ? w[n] : 1.0;
+    const double rr[4] = {cr.x, cr.y, cr.z, cr.w}, gr[4] = {cg.x, cg.y, cg.z, cg.w};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        if (Xo) Xo[q * N + n] = fl ? (double)X[q * NC + i] + rr[q] * wn : 0.0;
+        if (Xao) Xao[q * N + n] = sl >= 0 ? (double)Xa[q * NI + ia] + gr[q] * wn : 0.0;
     }
 }
 
@@ -2134,7 +2206,7 @@ struct GeomHost {
     int64_t ntile_max;
     // device buffers
     void *pin, *sig, *src, *a, *X0, *X1, *Xa, *coef, *prob;
-    double *part, *series, *spc, *spc0, *kc, *zout, *dout;
+    double *part, *series, *spc, *spc0, *kc, *zout, *dout, *vtail;
     int32_t* fidx;  // [N] index of a fluid node among the fluid nodes in lattice order, -1 on solid
     int32_t* fnode; // [nf] lattice index of a fluid node
     std::vector<int32_t> fidx_h;  // host copy
@@ -2171,6 +2243,7 @@ struct lbmp_mp {
     int K, gsz, variant;
     int uptake;           // out-of-equilibrium density propagation (no VACF)
     int64_t nblocks;
+    double drift_max = 0.0;  // watchdog bound
     hipGraph_t graph = nullptr;
     hipGraphExec_t gexec = nullptr;
 };
@@ -2239,6 +2312,7 @@ void carve_geom(GeomHost& g, Carver& c, int64_t tmax) {
     g.kc = c.take<double>(S * KC);
     g.zout = c.take<double>(S * 3 * (tmax + 1));
     g.dout = c.take<double>(S * 3 * (tmax + 1));
+    g.vtail = c.take<double>(S * 2 + 1);
 }
 
 // Carves the whole workspace; with a null base it only measures.
@@ -3057,6 +3131,7 @@ lbmp_status setup_all(lbmp_mp* h, hipStream_t s) {
     // LBMP_MASS_DRIFT_MAX overrides the watchdog threshold (tests force it)
     double drift_max = LBMP_MASS_DRIFT_MAX;
     if (const char* e = getenv("LBMP_MASS_DRIFT_MAX")) drift_max = atof(e);
+    h->drift_max = drift_max;
     Ctl c0{1, h->tmax, 0u, INT64_MAX, h->uptake ? 1.0 : 0.0, drift_max};
     LBMP_HIP(hipMemcpyAsync(h->ctl, &c0, sizeof c0, hipMemcpyHostToDevice, s));
     LBMP_HIP(hipStreamSynchronize(s));
@@ -3085,13 +3160,16 @@ lbmp_status check_mp(const lbmp_mp* h) {
 
 // The watchdog's verdict over the steps run so far (the stream is synchronised
 // by the caller).
+lbmp_status watchdog_verdict(const lbmp_mp* h, int64_t bad_t) {
+    if (bad_t <= h->steps)
+        return fail(LBMP_ENUMERIC, "total probability of a species left 1 by more than %.1e (or became non-finite) "
+                                   "at step %lld", h->drift_max, (long long)bad_t);
+    return LBMP_OK;
+}
 lbmp_status check_watchdog(lbmp_mp* h) {
     Ctl c;
     LBMP_HIP(hipMemcpy(&c, h->ctl, sizeof c, hipMemcpyDeviceToHost));
-    if (c.bad_t <= h->steps)
-        return fail(LBMP_ENUMERIC, "total probability of a species left 1 by more than %.1e (or became non-finite) "
-                                   "at step %lld", c.drift_max, (long long)c.bad_t);
-    return LBMP_OK;
+    return watchdog_verdict(h, c.bad_t);
 }
 
 }  // namespace
@@ -3293,30 +3371,24 @@ extern "C" lbmp_status mp_vacf(lbmp_mp* h, int geom, int64_t t0, int64_t count, 
     GeomHost& g = h->g[geom];
     hipStream_t s = h->stream;
     const int S = g.S;
-    const int64_t stride = h->tmax + 1;
-    if ((Z || D) && count > 0) {
-        k_vacf_series<<<(3 * S + 63) / 64, 64, 0, s>>>(g.series, S, h->steps, stride, g.spc0, g.zout, g.dout);
-        LBMP_HIP(hipGetLastError());
-        if (Z)
-            LBMP_HIP(hipMemcpy2DAsync(Z, count * 8, g.zout + t0, stride * 8, count * 8, 3 * (size_t)S,
-                                      hipMemcpyDeviceToHost, s));
-        if (D)
-            LBMP_HIP(hipMemcpy2DAsync(D, count * 8, g.dout + t0, stride * 8, count * 8, 3 * (size_t)S,
-                                      hipMemcpyDeviceToHost, s));
-    }
-    std::vector<double> last;
-    if (mass && h->steps > 0) {
-        last.resize((size_t)S * NRED);
-        LBMP_HIP(hipMemcpyAsync(last.data(), g.series + (h->steps - 1) * S * NRED, last.size() * 8,
-                                hipMemcpyDeviceToHost, s));
-    }
+    const int64_t m = Z || D ? count : 0;  // times wanted
+    k_vacf_series<<<dim3((unsigned)S, 3), VSC, 0, s>>>(g.series, S, h->steps, t0, m, g.spc0, h->ctl, g.zout, g.dout,
+                                                       g.vtail);
+    LBMP_HIP(hipGetLastError());
+    std::vector<double> tail(2 * (size_t)S + 1);
+    const size_t bytes = 3 * (size_t)S * m * 8;
+    if (Z && bytes) LBMP_HIP(hipMemcpyAsync(Z, g.zout, bytes, hipMemcpyDeviceToHost, s));
+    if (D && bytes) LBMP_HIP(hipMemcpyAsync(D, g.dout, bytes, hipMemcpyDeviceToHost, s));
+    LBMP_HIP(hipMemcpyAsync(tail.data(), g.vtail, tail.size() * 8, hipMemcpyDeviceToHost, s));
     LBMP_HIP(hipStreamSynchronize(s));
-    st = check_watchdog(h);
+    int64_t bad_t;
+    memcpy(&bad_t, &tail[2 * S], 8);
+    st = watchdog_verdict(h, bad_t);
     if (st != LBMP_OK) return st;
     if (mass)
         for (int sp = 0; sp < S; ++sp) {
-            mass[2 * sp] = g.rho_ref[sp] * g.sumw_f + (last.empty() ? 0.0 : last[sp * NRED + 3]);
-            mass[2 * sp + 1] = g.gam_ref[sp] * g.sumw_i + (last.empty() ? 0.0 : last[sp * NRED + 7]);
+            mass[2 * sp] = g.rho_ref[sp] * g.sumw_f + tail[2 * sp];
+            mass[2 * sp + 1] = g.gam_ref[sp] * g.sumw_i + tail[2 * sp + 1];
         }
     if (vbar)
         for (int i = 0; i < 3 * S; ++i) vbar[i] = g.V[i];
@@ -3355,42 +3427,37 @@ extern "C" lbmp_status mp_state(lbmp_mp* h, int geom, int species, double* X, do
     if (geom < 0 || geom >= h->ngeom) return fail(LBMP_EINVAL, "geometry index out of range");
     GeomHost& g = h->g[geom];
     if (species < 0 || species >= g.S) return fail(LBMP_EINVAL, "species index out of range");
-    const int64_t N = g.N, NI = g.NI, NIa = std::max<int64_t>(NI, 1);
+    const int64_t N = g.N, NIa = std::max<int64_t>(g.NI, 1);
     const int64_t t = h->steps + 1;
-    const size_t es = h->prec == LBMP_FP32 ? 4 : 8;
-    // fields of fluid nodes only (in lattice order) with the haloed LDS-DMA blocks
     const int64_t NC = compact_fields(h) ? g.nf : N;
-    const char* base = static_cast<const char*>((t & 1) ? g.X1 : g.X0) + (size_t)species * 4 * NC * es;
-    const char* abase = static_cast<const char*>(g.Xa) + (size_t)species * 4 * NIa * es;
-    std::vector<char> hx(4 * NC * es), ha(4 * NIa * es);
-    std::vector<int8_t> cls(N);
-    std::vector<int32_t> ilist(NIa);
-    LBMP_HIP(hipMemcpyAsync(hx.data(), base, hx.size(), hipMemcpyDeviceToHost, h->stream));
-    LBMP_HIP(hipMemcpyAsync(ha.data(), abase, ha.size(), hipMemcpyDeviceToHost, h->stream));
-    LBMP_HIP(hipMemcpyAsync(cls.data(), g.flow->d.cls, N, hipMemcpyDeviceToHost, h->stream));
-    if (NI > 0) LBMP_HIP(hipMemcpyAsync(ilist.data(), g.flow->d.ilist, NI * 4, hipMemcpyDeviceToHost, h->stream));
-    LBMP_HIP(hipStreamSynchronize(h->stream));
-    auto at = [&](const std::vector<char>& v, size_t i) {
-        return es == 4 ? (double)reinterpret_cast<const float*>(v.data())[i]
-                       : reinterpret_cast<const double*>(v.data())[i];
-    };
     const double rr = g.rho_ref[species], gr = g.gam_ref[species];
-    // where node n's fields and interface slot i's adsorbed fields are stored
-    const std::vector<int32_t>* map = !compact_fields(h) ? nullptr : (h->variant == 8 ? &g.gidx_h : &g.fidx_h);
-    const bool perm = h->variant == 8;
-    for (int q = 0; q < 4; ++q) {
-        const double cq = q == 0 ? 1.0 : g.V[3 * species + q - 1];
-        for (int64_t n = 0; n < N; ++n) {
-            const double wn = g.w.empty() ? 1.0 : g.w[n];
-            if (X) X[q * N + n] = cls[n] ? at(hx, q * NC + (map ? (*map)[n] : n)) + cq * rr * wn : 0.0;
-        }
-        if (Xads) {
-            for (int64_t n = 0; n < N; ++n) Xads[q * N + n] = 0.0;
-            for (int64_t i = 0; i < NI; ++i)
-                Xads[q * N + ilist[i]] =
-                    at(ha, q * NIa + (perm ? g.aperm_h[i] : i)) + cq * gr * (g.w.empty() ? 1.0 : g.w[ilist[i]]);
-        }
+    const double* const V = &g.V[3 * species];
+    const double4 cr = make_double4(rr, V[0] * rr, V[1] * rr, V[2] * rr);
+    const double4 cg = make_double4(gr, V[0] * gr, V[1] * gr, V[2] * gr);
+    // FP64 fields and the weights through the set-up scratch (free once the
+    // state exists)
+    double* const Xo = X ? h->setup_tmp : nullptr;
+    double* const Xao = Xads ? h->setup_tmp + 4 * N : nullptr;
+    double* w = nullptr;
+    if (!g.w.empty()) {
+        w = setup_bmu(h->setup_tmp, N) + N;
+        LBMP_HIP(hipMemcpyAsync(w, g.w.data(), N * 8, hipMemcpyHostToDevice, h->stream));
     }
+    const int32_t* const aperm = h->variant == 8 ? g.aperm : nullptr;
+    const unsigned nb = (unsigned)((N + BLK - 1) / BLK);
+    void* const Xs = (t & 1) ? g.X1 : g.X0;
+    auto out = [&](auto tag) {
+        using T = decltype(tag);
+        k_state_out<T><<<nb, BLK, 0, h->stream>>>(g.flow->d.cls, g.flow->d.slot, N, NC, NIa, cidx(h, g), aperm, w,
+                                                  static_cast<const T*>(Xs) + (int64_t)species * 4 * NC,
+                                                  static_cast<const T*>(g.Xa) + (int64_t)species * 4 * NIa, cr, cg,
+                                                  Xo, Xao);
+    };
+    if (h->prec == LBMP_FP32) out(float()); else out(double());
+    LBMP_HIP(hipGetLastError());
+    if (X) LBMP_HIP(hipMemcpyAsync(X, Xo, 4 * (size_t)N * 8, hipMemcpyDeviceToHost, h->stream));
+    if (Xads) LBMP_HIP(hipMemcpyAsync(Xads, Xao, 4 * (size_t)N * 8, hipMemcpyDeviceToHost, h->stream));
+    LBMP_HIP(hipStreamSynchronize(h->stream));
     return LBMP_OK;
 }
 
