@@ -8,7 +8,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblbmp.so")
-SOURCES = ["geometry.hip", "flow.hip", "mp.hip", "mlp.hip"]
+SOURCES = ["geometry.hip", "flow.hip", "chunks.hip", "mp.hip", "mlp.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [

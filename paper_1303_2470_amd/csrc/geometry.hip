@@ -70,41 +70,107 @@ __global__ void k_count(const int8_t* __restrict__ cls, int64_t N, uint32_t* __r
     }
 }
 
-// Exclusive scan of the per-block interfacial counts (one block); totals out.
-__global__ void k_scan_blocks(const uint32_t* __restrict__ nflu, uint32_t* __restrict__ nifc,
-                              int nb, int64_t* __restrict__ totals) {
-    __shared__ uint64_t part[256];
-    __shared__ uint64_t fpart[256];
-    int t = threadIdx.x;
-    // each thread owns a contiguous chunk
-    int chunk = (nb + 255) / 256;
-    int lo = t * chunk, hi = min(nb, lo + chunk);
-    uint64_t s = 0, f = 0;
-    for (int k = lo; k < hi; ++k) {
-        s += nifc[k];
-        f += nflu[k];
+// Exclusive scans of two arrays of counts in place (one block); totals out.
+// Each thread scans 8 neighbouring counts of a stretch of 8,192 and the
+// threads' sums are scanned across the block, stretch after stretch.
+constexpr int SCT = 1024, SCV = 8;
+// 8 counts from i, zeros from n on; 16-byte accesses where they all exist (the
+// arrays are 256-byte aligned and i a multiple of 8).
+__device__ __forceinline__ void load_counts(const uint32_t* p, int64_t i, int64_t n, uint32_t (&v)[SCV]) {
+    if (i + SCV <= n) {
+        const uint4 x = *reinterpret_cast<const uint4*>(p + i), y = *reinterpret_cast<const uint4*>(p + i + 4);
+        v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
+        v[4] = y.x; v[5] = y.y; v[6] = y.z; v[7] = y.w;
+    } else {
+#pragma unroll
+        for (int k = 0; k < SCV; ++k) v[k] = i + k < n ? p[i + k] : 0;
     }
-    part[t] = s;
-    fpart[t] = f;
-    __syncthreads();
-    if (t == 0) {
-        uint64_t acc = 0, facc = 0;
-        for (int k = 0; k < 256; ++k) {
-            uint64_t v = part[k];
-            part[k] = acc;
-            acc += v;
-            facc += fpart[k];
+}
+__device__ __forceinline__ void store_counts(uint32_t* p, int64_t i, int64_t n, uint32_t add, const uint32_t (&v)[SCV]) {
+    if (i + SCV <= n) {
+        *reinterpret_cast<uint4*>(p + i) = make_uint4(add + v[0], add + v[1], add + v[2], add + v[3]);
+        *reinterpret_cast<uint4*>(p + i + 4) = make_uint4(add + v[4], add + v[5], add + v[6], add + v[7]);
+    } else {
+#pragma unroll
+        for (int k = 0; k < SCV; ++k)
+            if (i + k < n) p[i + k] = add + v[k];
+    }
+}
+
+__global__ void __launch_bounds__(SCT) k_scan_counts(uint32_t* __restrict__ a, uint32_t* __restrict__ b, int n,
+                                                     int64_t* __restrict__ totals) {
+    __shared__ uint32_t wa[SCT / 64], wb[SCT / 64];
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    uint32_t ca = 0, cb = 0;
+    for (int64_t base = 0; base < n; base += SCT * SCV) {
+        const int64_t i0 = base + (int64_t)t * SCV;
+        uint32_t va[SCV], vb[SCV], sa = 0, sb = 0;
+        load_counts(a, i0, n, va);
+        load_counts(b, i0, n, vb);
+#pragma unroll
+        for (int k = 0; k < SCV; ++k) {
+            uint32_t x = va[k], y = vb[k];
+            va[k] = sa;
+            vb[k] = sb;
+            sa += x;
+            sb += y;
         }
-        totals[0] = (int64_t)facc;
-        totals[1] = (int64_t)acc;
+        uint32_t ia = sa, ib = sb;
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t ua = __shfl_up(ia, off, 64), ub = __shfl_up(ib, off, 64);
+            if (lane >= off) {
+                ia += ua;
+                ib += ub;
+            }
+        }
+        if (lane == 63) {
+            wa[wv] = ia;
+            wb[wv] = ib;
+        }
+        __syncthreads();
+        uint32_t pa = ca + ia - sa, pb = cb + ib - sb;
+        for (int w = 0; w < SCT / 64; ++w) {
+            if (w < wv) {
+                pa += wa[w];
+                pb += wb[w];
+            }
+            ca += wa[w];
+            cb += wb[w];
+        }
+        store_counts(a, i0, n, pa, va);
+        store_counts(b, i0, n, pb, vb);
+        __syncthreads();
     }
+    if (t == 0) {
+        totals[0] = (int64_t)ca;
+        totals[1] = (int64_t)cb;
+    }
+}
+
+void scan_counts(uint32_t* a, uint32_t* b, int n, int64_t* totals, hipStream_t s) {
+    k_scan_counts<<<1, SCT, 0, s>>>(a, b, n, totals);
+}
+
+// fidx[n] = rank of fluid node n among the fluid nodes (ascending node index),
+// -1 on solid nodes; fnode the inverse. boff: fluid nodes before each block.
+__global__ void __launch_bounds__(CBLK) k_rank_fluid(const int8_t* __restrict__ cls, int64_t N,
+                                                     const uint32_t* __restrict__ boff, int32_t* __restrict__ fidx,
+                                                     int32_t* __restrict__ fnode) {
+    __shared__ uint32_t wcount[CBLK / 64];
+    const int64_t n = (int64_t)blockIdx.x * CBLK + threadIdx.x;
+    const bool is = n < N && cls[n] != 0;
+    const uint64_t b = __ballot(is);
+    const int lane = threadIdx.x & 63, w = threadIdx.x / 64;
+    if (lane == 0) wcount[w] = __popcll(b);
     __syncthreads();
-    uint64_t acc = part[t];
-    for (int k = lo; k < hi; ++k) {
-        uint32_t v = nifc[k];
-        nifc[k] = (uint32_t)acc;
-        acc += v;
-    }
+    uint32_t r = boff[blockIdx.x] + __popcll(b & ((1ull << lane) - 1));
+    for (int k = 0; k < w; ++k) r += wcount[k];
+    if (n < N) fidx[n] = is ? (int32_t)r : -1;
+    if (is) fnode[r] = (int32_t)n;
+}
+
+void rank_fluid(const lbmp_flow* f, int32_t* fidx, int32_t* fnode, hipStream_t s) {
+    k_rank_fluid<<<(unsigned)((f->N + CBLK - 1) / CBLK), CBLK, 0, s>>>(f->d.cls, f->N, f->d.blk, fidx, fnode);
 }
 
 // slot[n] = rank of n among interfacial nodes (ascending node index), -1 else.
@@ -189,7 +255,7 @@ lbmp_status build_geometry(const lbmp_geometry* g, Carver& c, FlowLayout& L, hip
     k_classify<<<(unsigned)((N + 255) / 256), 256, 0, s>>>(L.solid, L.cls, g->nx, g->ny, g->nz, nlinks);
     LBMP_HIP(hipGetLastError());
     k_count<<<nb, CBLK, 0, s>>>(L.cls, N, L.blk, blk2);
-    k_scan_blocks<<<1, 256, 0, s>>>(L.blk, blk2, nb, L.counts);
+    scan_counts(L.blk, blk2, nb, L.counts, s);
     k_scatter<<<nb, CBLK, 0, s>>>(L.cls, N, blk2, L.slot, L.ilist);
     LBMP_HIP(hipGetLastError());
     int64_t h[2];

@@ -3,6 +3,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <cmath>
 #include <cstdint>
 #include <cstdio>
 #include <string>
@@ -73,7 +75,7 @@ struct FlowLayout {
     int32_t* ilist;  // node index per interface slot (ascending)
     double* u;       // [3][N]
     int64_t* counts; // [2] fluid, interface
-    uint32_t* blk;   // per-1024-node block counts / offsets, 2 arrays
+    uint32_t* blk;   // fluid nodes before each 1,024-node block
 };
 
 struct lbmp_flow_impl;
@@ -95,4 +97,21 @@ lbmp_status build_geometry(const lbmp_geometry* g, Carver& c, FlowLayout& L, hip
                            int64_t* nf, int64_t* ni);
 size_t geometry_bytes(int64_t N);
 lbmp_status validate_geometry(const lbmp_geometry* g);
+// Exclusive scan of two count arrays in place (one block); totals[0..1] receive the sums.
+void scan_counts(uint32_t* a, uint32_t* b, int n, int64_t* totals, hipStream_t s);
+// Compact numbering of the fluid nodes in lattice order: fidx[N] (-1 on solid
+// nodes) and fnode[nf]; asynchronous on s.
+void rank_fluid(const lbmp_flow* f, int32_t* fidx, int32_t* fnode, hipStream_t s);
+
+// Tables of the gathered-chunk step kernel, see chunks.hip.
+struct ChunkTables {
+    int32_t *gidx, *gnode, *gaslot, *ghsrc, *aperm;
+    int4* gch;
+    uint16_t* gnbr;
+};
+// Ordering tiles of tile[0..2] nodes, chunks of up to CH nodes (a multiple of
+// 64, at most 512), at most cap of them; ghsrc holds CH quads per chunk.
+// *nch = 0 when some chunk does not fit even cut short.
+lbmp_status build_chunks(const lbmp_flow* f, const int tile[3], int CH, int zslot, int64_t cap, void* scratch,
+                         size_t scratch_bytes, const ChunkTables& T, hipStream_t s, int64_t* nch);
 }  // namespace lbmp

@@ -36,6 +36,7 @@
 #include <cstdlib>
 #include <cmath>
 #include <map>
+#include <mutex>
 #include <tuple>
 #include <type_traits>
 
@@ -1956,7 +1957,7 @@ __global__ void k_links(const int8_t* __restrict__ cls, const double* __restrict
                         T* __restrict__ pin, double* __restrict__ sig, T* __restrict__ src, T* __restrict__ a,
                         double* __restrict__ b64, double* __restrict__ src64,
                         double* __restrict__ part) {
-    __shared__ double lds[SETUP_RED * BLK];
+    __shared__ double lds[SETUP_RED * (BLK + 1)];  // rows a bank apart
     const int64_t N = (int64_t)nx * ny * nz;
     int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     double v[SETUP_RED] = {0, 0, 0, 0, 0, 0, INFINITY, 0.0, INFINITY, INFINITY, 0, 0};
@@ -2007,12 +2008,13 @@ __global__ void k_links(const int8_t* __restrict__ cls, const double* __restrict
         }
     }
     const int tid = threadIdx.x;
-    for (int k = 0; k < SETUP_RED; ++k) lds[k * BLK + tid] = v[k];
+    for (int k = 0; k < SETUP_RED; ++k) lds[k * (BLK + 1) + tid] = v[k];
     __syncthreads();
     if (tid < SETUP_RED) {
-        double r = lds[tid * BLK];
+        double r = lds[tid * (BLK + 1)];
+#pragma unroll 8
         for (int j = 1; j < BLK; ++j) {
-            double w = lds[tid * BLK + j];
+            double w = lds[tid * (BLK + 1) + j];
             if (tid == 6 || tid == 8 || tid == 9) r = fmin(r, w);
             else if (tid == 7) r = fmax(r, w);
             else r += w;
@@ -2021,17 +2023,53 @@ __global__ void k_links(const int8_t* __restrict__ cls, const double* __restrict
     }
 }
 
-__global__ void k_setup_final(const double* __restrict__ part, int nb, double* __restrict__ out) {
-    const int k = threadIdx.x;
-    if (k >= SETUP_RED || blockIdx.x != 0) return;
-    double r = part[k];
-    for (int b = 1; b < nb; ++b) {
-        double w = part[(int64_t)b * SETUP_RED + k];
-        if (k == 6 || k == 8 || k == 9) r = fmin(r, w);
-        else if (k == 7) r = fmax(r, w);
-        else r += w;
+// The blocks' values combined in block order (the sums' rounding enters the
+// reference weights, which checkpoints are compared by). One thread follows
+// each value, in a wave of its kind (sums, minima, maximum); the block stages
+// SFB blocks at a time in LDS, so the serial chain waits for an addition and
+// not for a load from memory at every block (65,536 blocks: 23.5 -> 0.94 ms).
+constexpr int SFB = 128;
+
+__global__ void __launch_bounds__(256) k_setup_final(const double* __restrict__ part, int nb,
+                                                     double* __restrict__ out) {
+    __shared__ double st[2][SFB * SETUP_RED];
+    const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6), k = tid & 63;
+    const bool mine = k < SETUP_RED && (k == 7 ? 2 : (k == 6 || k == 8 || k == 9) ? 1 : 0) == wv;
+    constexpr int PT = (SFB * SETUP_RED + 255) / 256, U = 16;
+    double v[PT], r = wv == 0 ? 0.0 : part[min(k, SETUP_RED - 1)];
+    auto fetch = [&](int b0) {
+        const int n = min(SFB, nb - b0) * SETUP_RED;
+#pragma unroll
+        for (int i = 0; i < PT; ++i) v[i] = tid + i * 256 < n ? part[(int64_t)b0 * SETUP_RED + tid + i * 256] : 0.0;
+    };
+    fetch(0);
+    int par = 0;
+    for (int b0 = 0; b0 < nb; b0 += SFB, par ^= 1) {
+#pragma unroll
+        for (int i = 0; i < PT; ++i)
+            if (tid + i * 256 < SFB * SETUP_RED) st[par][tid + i * 256] = v[i];
+        __syncthreads();
+        if (b0 + SFB < nb) fetch(b0 + SFB);  // on its way while the chain below runs
+        if (mine) {
+            const int n = min(SFB, nb - b0);
+            const double* const p = st[par] + k;
+            auto chain = [&](auto op) {
+                int b = 0;
+                for (; b + U <= n; b += U) {
+                    double x[U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) x[u] = p[(b + u) * SETUP_RED];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) r = op(r, x[u]);
+                }
+                for (; b < n; ++b) r = op(r, p[b * SETUP_RED]);
+            };
+            if (wv == 0) chain([](double a, double b) { return a + b; });  // 0 + the first block's: exact
+            else if (wv == 1) chain([](double a, double b) { return fmin(a, b); });
+            else chain([](double a, double b) { return fmax(a, b); });
+        }
     }
-    out[k] = r;
+    if (mine) out[k] = r;
 }
 
 // State at t = 1 (deviations): density rho_ref*src; first moments
@@ -2188,6 +2226,7 @@ struct TuneVal {
     int K, gsz, variant;
 };
 static std::map<TuneKey, TuneVal> g_tune_cache;
+static std::mutex g_tune_mu;
 
 struct GeomHost {
     const lbmp_flow* flow;
@@ -2198,6 +2237,8 @@ struct GeomHost {
     double A[3], B[3];
     double min_p, max_u, min_stay_bulk, min_stay_iface, pa_max;
     std::vector<double> V, Z0;  // [S][3]
+    std::vector<double> up64;   // species constants on their way to the device during set-up
+    std::vector<char> upT;
     // charged tracers: beta mu^ex per node (empty: neutral) and the relative
     // Eq. 11 weights exp(-(beta mu^ex - its minimum over fluid nodes)); the
     // weighted fluid and interfacial totals (N_F and N_I when neutral)
@@ -2209,18 +2250,16 @@ struct GeomHost {
     double *part, *series, *spc, *spc0, *kc, *zout, *dout, *vtail;
     int32_t* fidx;  // [N] index of a fluid node among the fluid nodes in lattice order, -1 on solid
     int32_t* fnode; // [nf] lattice index of a fluid node
-    std::vector<int32_t> fidx_h;  // host copy
     // gathered chunks (variant 8): the compact order of their fields (gidx,
     // tiles of 32 x 4 x 4 nodes), chunk table, halo quads, neighbour slots, lattice
     // index and adsorbed-field index per compact node, adsorbed-field index
-    // per interface slot (aperm); host copies of gidx and aperm
+    // per interface slot (aperm); built when the variant is chosen or timed
     int32_t *gidx, *gnode, *gaslot, *ghsrc, *aperm;
     int4* gch;
     uint16_t* gnbr;
     int64_t nch = 0;
     int gnh = 2;  // threads per block / 256 of the chunk tables (LBMP_GATHER_NH, default 2)
-    bool gather_ok = false;
-    std::vector<int32_t> gidx_h, aperm_h;
+    bool gather_built = false, gather_ok = false;
 };
 
 }  // namespace lbmp
@@ -2231,6 +2270,8 @@ struct lbmp_mp {
     int64_t tmax, steps;
     hipStream_t stream;
     std::vector<lbmp::GeomHost> g;
+    std::vector<int32_t> work_h;  // host copies of work and of the initial ctl
+    lbmp::Ctl ctl0;
     void* geoms_dev;
     lbmp::Ctl* ctl;
     int32_t* work;
@@ -2631,6 +2672,40 @@ void tune_cache_write(const std::string& key, const TuneVal& v, double ms) {
     fclose(f);
 }
 
+// Tables of the gathered-chunk blocks (variant 8) for every geometry, through
+// the set-up scratch (before the link tables are formed there). The compact
+// order runs over tiles of GTX x GTY x GTZ nodes, long in x, so that the halo
+// a chunk pulls across its y and z faces comes in runs of up to GTX
+// consecutive compact nodes (whole cache lines) and its x faces are small. A
+// geometry with a chunk whose quads exceed the region even when cut short
+// leaves gather_ok false (the variant is then not offered).
+lbmp_status build_gather(lbmp_mp* h) {
+    if (h->prec != LBMP_FP32) return LBMP_OK;
+    // LBMP_GATHER_TILE="tx,ty,tz" overrides the tile shape (experiments)
+    int tile[3] = {GTX, GTY, GTZ};
+    if (const char* e = getenv("LBMP_GATHER_TILE")) {
+        int a = 0, b = 0, c = 0;
+        if (sscanf(e, "%d,%d,%d", &a, &b, &c) == 3 && a > 0 && b > 0 && c > 0) {
+            tile[0] = a;
+            tile[1] = b;
+            tile[2] = c;
+        }
+    }
+    for (auto& g : h->g) {
+        if (g.gather_built) continue;
+        g.gnh = 2;
+        if (const char* e = getenv("LBMP_GATHER_NH")) g.gnh = atoi(e) == 1 ? 1 : 2;
+        const int zs = g.gnh == 1 ? GatherShape<1>::ZSLOT : GatherShape<2>::ZSLOT;
+        const ChunkTables T{g.gidx, g.gnode, g.gaslot, g.ghsrc, g.aperm, g.gch, g.gnbr};
+        lbmp_status st = build_chunks(g.flow, tile, g.gnh * BLK, zs, gather_chunk_cap(g.nf), h->setup_tmp,
+                                      (size_t)setup_doubles(g.N) * 8, T, h->stream, &g.nch);
+        if (st != LBMP_OK) return st;
+        g.gather_built = true;
+        g.gather_ok = g.nch > 0;
+    }
+    return LBMP_OK;
+}
+
 // Whether a (variant, K, species per block) choice is allowed for the handle.
 bool tile_allowed(const lbmp_mp* h, int v, int K, int gs) {
     const bool ok01 = (v == 0 || v == 1) && (K == 1 || K == 2) && gs >= 1;
@@ -2649,29 +2724,49 @@ bool tile_allowed(const lbmp_mp* h, int v, int K, int gs) {
     return ok01 || ok2 || ok3 || ok9 || ok10;
 }
 
-// Pick (K, species per block) by timing steps of each candidate on the
-// set-up tables before the state exists: a short screening run of every
-// candidate, then a longer steady-state run (warm caches and clocks) of the
-// fastest few. Results are cached per (precision, shapes) for the life of the
-// process and on disk (see tune_cache_path).
-lbmp_status autotune(lbmp_mp* h) {
+TuneKey tune_key(const lbmp_mp* h) {
     TuneKey key{h->prec, {}};
-    int64_t work = 0;
-    int maxS = 0;
-    for (auto& g : h->g) {
+    for (const auto& g : h->g)
         key.shape.insert(key.shape.end(), {g.flow->nx, g.flow->ny, g.flow->nz, g.S, g.nf, g.NI});
-        work += g.nf * g.S;
-        maxS = std::max(maxS, g.S);
-    }
+    return key;
+}
+int max_species(const lbmp_mp* h) {
+    int m = 0;
+    for (const auto& g : h->g) m = std::max(m, g.S);
+    return m;
+}
+void remember(const TuneKey& key, const TuneVal& v) {
+    std::lock_guard<std::mutex> lk(g_tune_mu);
+    g_tune_cache[key] = v;
+}
+
+// The step kernel where nothing needs timing: pinned, in the process's or the
+// on-disk cache, or a launch-bound size. *chosen stays false otherwise. Runs
+// before any table is formed (variant 8's tables pass through the scratch).
+lbmp_status choose_tile(lbmp_mp* h, bool* chosen) {
+    *chosen = false;
+    const int maxS = max_species(h);
+    // the cached choice must still be allowed: a medium with the same counts
+    // can have a chunk that does not fit
+    auto take = [&](const TuneVal& v) -> lbmp_status {
+        if (v.variant == 8) {
+            const lbmp_status st = build_gather(h);
+            if (st != LBMP_OK) return st;
+        }
+        if (!tile_allowed(h, v.variant, v.K, v.gsz)) return LBMP_OK;
+        h->K = v.K;
+        h->gsz = v.variant == 2 ? v.gsz : std::min(v.gsz, std::max(1, maxS));
+        h->variant = v.variant;
+        *chosen = true;
+        return upload(h);
+    };
     // LBMP_TILE="variant,K,species_per_block" pins the choice (tests, experiments)
     if (const char* env = getenv("LBMP_TILE")) {
         int v = 0, K = 1, gs = 1;
         const int nread = sscanf(env, "%d,%d,%d", &v, &K, &gs);
-        if (nread == 3 && tile_allowed(h, v, K, gs)) {
-            h->variant = v;
-            h->K = K;
-            h->gsz = v == 2 ? gs : std::min(gs, std::max(1, maxS));
-            return upload(h);
+        if (nread == 3) {
+            const lbmp_status st = take({K, gs, v});
+            if (st != LBMP_OK || *chosen) return st;
         }
         return fail(LBMP_EINVAL, "LBMP_TILE must be 'variant,K,species_per_block': variant 0|1 with K 1|2, "
                                  "variant 2 with K = z-segment and 1|2|4 species per block, or variant 3 "
@@ -2682,35 +2777,44 @@ lbmp_status autotune(lbmp_mp* h) {
                                  "or variant 9 with K = 1, 2 or 4 quantities per block (1 for uptake) and 1 species, or "
                                  "variant 10 with K = 1 and 1 species (at most 2,048 fluid nodes in every geometry, 1,536 in FP64)");
     }
-    auto it = g_tune_cache.find(key);
-    if (it != g_tune_cache.end()) {
-        h->K = it->second.K;
-        h->gsz = it->second.gsz;
-        h->variant = it->second.variant;
-        return upload(h);
-    }
-    const std::string skey = tune_key_string(h);
+    const TuneKey key = tune_key(h);
+    TuneVal v;
+    bool known;
     {
-        TuneVal dv;
-        if (tune_cache_read(skey, &dv) && tile_allowed(h, dv.variant, dv.K, dv.gsz)) {
-            h->K = dv.K;
-            h->gsz = dv.variant == 2 ? dv.gsz : std::min(dv.gsz, std::max(1, maxS));
-            h->variant = dv.variant;
-            g_tune_cache[key] = {h->K, h->gsz, h->variant};
-            return upload(h);
+        std::lock_guard<std::mutex> lk(g_tune_mu);
+        const auto it = g_tune_cache.find(key);
+        known = it != g_tune_cache.end();
+        if (known) v = it->second;
+    }
+    if (!known) known = tune_cache_read(tune_key_string(h), &v);
+    if (known) {
+        const lbmp_status st = take(v);
+        if (st != LBMP_OK || *chosen) {
+            if (*chosen) remember(key, {h->K, h->gsz, h->variant});
+            return st;
         }
     }
+    int64_t work = 0;
+    for (const auto& g : h->g) work += g.nf * g.S;
     // Launch-bound sizes, where timing candidates would cost more than any of
     // them could save: the resident kernel wherever the fields fit its blocks
     // (0.7 against 12 us a step on a 32-node slit), else one quantity per block
     // (12 against 21-26 us a step for variant 0 on 17 k nodes x 3 species).
     if (work < (1 << 16)) {
-        h->gsz = 1;
-        h->K = 1;
-        h->variant = tile_allowed(h, 10, 1, 1) ? 10 : 9;
-        g_tune_cache[key] = {h->K, h->gsz, h->variant};
-        return upload(h);
+        v = {1, 1, tile_allowed(h, 10, 1, 1) ? 10 : 9};
+        remember(key, v);
+        return take(v);
     }
+    return build_gather(h);  // a candidate of the tuner
+}
+
+// Pick (K, species per block) by timing steps of each candidate on the
+// set-up tables before the state exists: a short screening run of every
+// candidate, then a longer steady-state run (warm caches and clocks) of the
+// fastest few. Results are cached per (precision, shapes) for the life of the
+// process and on disk (see tune_cache_path).
+lbmp_status autotune(lbmp_mp* h) {
+    const int maxS = max_species(h);
     std::vector<TuneVal> cand;
     for (int v : {0, 1})
         for (int K : {1, 2})
@@ -2790,8 +2894,8 @@ lbmp_status autotune(lbmp_mp* h) {
     h->K = bv.K;
     h->gsz = bv.gsz;
     h->variant = bv.variant;
-    g_tune_cache[key] = bv;
-    tune_cache_write(skey, bv, best);
+    remember(tune_key(h), bv);
+    tune_cache_write(tune_key_string(h), bv, best);
     return upload(h);
 }
 
@@ -2818,7 +2922,7 @@ lbmp_status build_links(lbmp_mp* h, GeomHost& g, hipStream_t s, double* fin_host
     k_pout<<<nb, BLK, 0, s>>>(f->d.cls, f->d.u, f->nx, f->ny, f->nz, g.lam, bmu, pout);
     k_links<T><<<nb, BLK, 0, s>>>(f->d.cls, pout, f->d.u, f->nx, f->ny, f->nz, w, (T*)g.pin, (double*)g.sig,
                                   (T*)g.src, (T*)g.a, b64, src64, part);
-    k_setup_final<<<1, 64, 0, s>>>(part, nb, fin);
+    k_setup_final<<<1, 256, 0, s>>>(part, nb, fin);
     LBMP_HIP(hipGetLastError());
     if (fin_host) {
         LBMP_HIP(hipMemcpyAsync(fin_host, fin, SETUP_RED * 8, hipMemcpyDeviceToHost, s));
@@ -2841,9 +2945,11 @@ lbmp_status species_constants(lbmp_mp* h, GeomHost& g, const double* r, hipStrea
     g.min_stay_iface = r[9];
     g.sumw_f = r[10];  // sums of 1 over the fluid and interfacial nodes when neutral: N_F, N_I exactly
     g.sumw_i = r[11];
-    std::vector<double> spc(S * 5), spc0(S * 7, 0.0);
-    std::vector<T> coef(S * 4), prob(S * 2);
-    std::vector<double> kc(S * KC, 0.0);
+    // kept in g until the set-up's last synchronisation
+    g.up64.assign((size_t)S * (5 + 7 + KC), 0.0);
+    g.upT.assign((size_t)S * 6 * sizeof(T), 0);
+    double *const spc = g.up64.data(), *const spc0 = spc + S * 5, *const kc = spc0 + S * 7;
+    T *const coef = reinterpret_cast<T*>(g.upT.data()), *const prob = coef + S * 4;
     g.rho_ref.resize(S);
     g.gam_ref.resize(S);
     g.V.assign(3 * S, 0.0);
@@ -2881,12 +2987,11 @@ lbmp_status species_constants(lbmp_mp* h, GeomHost& g, const double* r, hipStrea
     const double min_stay = std::min(g.min_stay_bulk, g.min_stay_iface - g.pa_max);
     if (min_stay < 0.0)
         return fail(LBMP_EPROB, "negative stay probability %.3e (sum p_i + p_a > 1)", min_stay);
-    LBMP_HIP(hipMemcpyAsync(g.spc, spc.data(), spc.size() * 8, hipMemcpyHostToDevice, s));
-    LBMP_HIP(hipMemcpyAsync(g.spc0, spc0.data(), spc0.size() * 8, hipMemcpyHostToDevice, s));
-    LBMP_HIP(hipMemcpyAsync(g.coef, coef.data(), coef.size() * sizeof(T), hipMemcpyHostToDevice, s));
-    LBMP_HIP(hipMemcpyAsync(g.prob, prob.data(), prob.size() * sizeof(T), hipMemcpyHostToDevice, s));
-    LBMP_HIP(hipMemcpyAsync(g.kc, kc.data(), kc.size() * 8, hipMemcpyHostToDevice, s));
-    LBMP_HIP(hipStreamSynchronize(s));
+    LBMP_HIP(hipMemcpyAsync(g.spc, spc, (size_t)S * 5 * 8, hipMemcpyHostToDevice, s));
+    LBMP_HIP(hipMemcpyAsync(g.spc0, spc0, (size_t)S * 7 * 8, hipMemcpyHostToDevice, s));
+    LBMP_HIP(hipMemcpyAsync(g.coef, coef, (size_t)S * 4 * sizeof(T), hipMemcpyHostToDevice, s));
+    LBMP_HIP(hipMemcpyAsync(g.prob, prob, (size_t)S * 2 * sizeof(T), hipMemcpyHostToDevice, s));
+    LBMP_HIP(hipMemcpyAsync(g.kc, kc, (size_t)S * KC * 8, hipMemcpyHostToDevice, s));
     return LBMP_OK;
 }
 
@@ -2921,161 +3026,6 @@ lbmp_status compact_links(lbmp_mp* h, GeomHost& g, hipStream_t s) {
     return st;
 }
 
-// Index of every fluid node among the fluid nodes in lattice order (-1 on
-// solid nodes), the address of its fields in compact storage.
-lbmp_status build_fidx(GeomHost& g, hipStream_t s) {
-    std::vector<int8_t> cls(g.N);
-    LBMP_HIP(hipMemcpyAsync(cls.data(), g.flow->d.cls, g.N, hipMemcpyDeviceToHost, s));
-    LBMP_HIP(hipStreamSynchronize(s));
-    std::vector<int32_t> fi(g.N), fn;
-    fn.reserve(g.nf);
-    for (int64_t n = 0; n < g.N; ++n) {
-        fi[n] = cls[n] ? (int32_t)fn.size() : -1;
-        if (cls[n]) fn.push_back((int32_t)n);
-    }
-    const int64_t c = (int64_t)fn.size();
-    if (c != g.nf) return fail(LBMP_ESTATE, "fluid node count %lld differs from the flow's %lld", (long long)c,
-                               (long long)g.nf);
-    LBMP_HIP(hipMemcpyAsync(g.fidx, fi.data(), g.N * 4, hipMemcpyHostToDevice, s));
-    LBMP_HIP(hipMemcpyAsync(g.fnode, fn.data(), g.nf * 4, hipMemcpyHostToDevice, s));
-    LBMP_HIP(hipStreamSynchronize(s));
-    g.fidx_h = std::move(fi);
-    return LBMP_OK;
-}
-
-// Tables of the gathered-chunk blocks (variant 8) for geometry g. The compact
-// order runs over tiles of GTX x GTY x GTZ lattice nodes and, within a
-// tile, over its fluid nodes in lattice order; chunk c takes compact
-// nodes base .. base + C - 1 (C up to the block's threads). Its halo, the
-// fluid nodes outside the chunk its nodes pull from (r - c_k), is covered by
-// quads of 4 consecutive compact nodes, each started at the lowest halo node
-// the quads before it leave out; each node's 18 arrivals get their region
-// slot: the chunk node's own position, 4 (ceil(C / 4) + q) + offset for a
-// halo node in quad q, the zero slot for a solid r - c_k. A chunk whose quads
-// exceed the region even when cut short leaves gather_ok false (the tuner
-// then does not offer the variant for the workload).
-lbmp_status build_gather(GeomHost& g, hipStream_t s) {
-    g.gather_ok = false;
-    const lbmp_flow* f = g.flow;
-    const int nx = f->nx, ny = f->ny, nz = f->nz;
-    const int64_t N = g.N;
-    std::vector<int8_t> cls(N);
-    std::vector<int32_t> slot(N);
-    LBMP_HIP(hipMemcpyAsync(cls.data(), f->d.cls, N, hipMemcpyDeviceToHost, s));
-    LBMP_HIP(hipMemcpyAsync(slot.data(), f->d.slot, N * 4, hipMemcpyDeviceToHost, s));
-    LBMP_HIP(hipStreamSynchronize(s));
-    // tiles of GTX x GTY x GTZ nodes, x fastest then y, z; long in x, so that
-    // the halo a chunk pulls across its y and z faces comes in runs of up to
-    // GTX consecutive compact nodes (whole cache lines) and its x faces are small
-    // LBMP_GATHER_TILE="tx,ty,tz" overrides the tile shape (experiments)
-    int gtx = GTX, gty = GTY, gtz = GTZ;
-    if (const char* e = getenv("LBMP_GATHER_TILE")) {
-        int a = 0, b = 0, c = 0;
-        if (sscanf(e, "%d,%d,%d", &a, &b, &c) == 3 && a > 0 && b > 0 && c > 0) {
-            gtx = a;
-            gty = b;
-            gtz = c;
-        }
-    }
-    std::vector<int32_t> gidx(N, -1), gnode;
-    gnode.reserve(g.nf);
-    for (int tz = 0; tz < nz; tz += gtz)
-        for (int ty = 0; ty < ny; ty += gty)
-            for (int tx = 0; tx < nx; tx += gtx)
-                for (int z = tz; z < std::min(nz, tz + gtz); ++z)
-                    for (int y = ty; y < std::min(ny, ty + gty); ++y)
-                        for (int x = tx; x < std::min(nx, tx + gtx); ++x) {
-                            const int64_t n = x + (int64_t)nx * (y + (int64_t)ny * z);
-                            if (cls[n]) {
-                                gidx[n] = (int32_t)gnode.size();
-                                gnode.push_back((int32_t)n);
-                            }
-                        }
-    const int64_t NF = (int64_t)gnode.size();
-    if (NF != g.nf) return fail(LBMP_ESTATE, "fluid node count %lld differs from the flow's %lld", (long long)NF,
-                                (long long)g.nf);
-    std::vector<int32_t> gaslot(NF, -1), aperm(std::max<int64_t>(g.NI, 1), 0);
-    int32_t ai = 0;
-    for (int64_t i = 0; i < NF; ++i)
-        if (cls[gnode[i]] == 2) {
-            gaslot[i] = ai;
-            aperm[slot[gnode[i]]] = ai++;
-        }
-    g.gnh = 2;
-    if (const char* e = getenv("LBMP_GATHER_NH")) g.gnh = atoi(e) == 1 ? 1 : 2;
-    const int64_t CH = (int64_t)g.gnh * BLK;                      // nodes per chunk, region quads
-    const int64_t ZS = g.gnh == 1 ? GatherShape<1>::ZSLOT : GatherShape<2>::ZSLOT;
-    const int64_t cap = gather_chunk_cap(NF);
-    std::vector<int4> chs;
-    std::vector<int32_t> hsrc, halo, hq, pos(NF, -1);
-    std::vector<uint16_t> nbr((size_t)NL * NF);
-    auto from = [&](int64_t n, int k) {  // lattice index of r - c_k (periodic)
-        const int x = (int)(n % nx), y = (int)((n / nx) % ny), z = (int)(n / ((int64_t)nx * ny));
-        return (int64_t)wrapi(x - lcx(k), nx) + (int64_t)nx * (wrapi(y - lcy(k), ny) + (int64_t)ny * wrapi(z - lcz(k), nz));
-    };
-    auto halo_of = [&](int64_t base, int64_t C) {
-        halo.clear();
-        for (int64_t i = base; i < base + C; ++i)
-            for (int k = 0; k < NL; ++k) {
-                const int64_t m = from(gnode[i], k);
-                if (!cls[m]) continue;
-                const int32_t j = gidx[m];
-                if (j < base || j >= base + C) halo.push_back(j);
-            }
-        std::sort(halo.begin(), halo.end());
-        halo.erase(std::unique(halo.begin(), halo.end()), halo.end());
-        hq.clear();
-        for (const int32_t h : halo)
-            if (hq.empty() || h >= hq.back() + 4) hq.push_back(h);
-    };
-    // quads the region holds for chunk nodes and halo (the last quad stays zero)
-    auto quads = [&](int64_t C) { return (C + 3) / 4 + (int64_t)hq.size(); };
-    for (int64_t base = 0; base < NF;) {
-        // the longest chunk (up to CH nodes, in steps of 64) whose quads fit
-        int64_t C = std::min<int64_t>(CH, NF - base);
-        halo_of(base, C);
-        while (quads(C) > CH - 1 && C > 64) {
-            C = std::max<int64_t>(64, C - 64);
-            halo_of(base, C);
-        }
-        const int64_t Cq = (C + 3) / 4, H = (int64_t)hq.size();
-        if (quads(C) > CH - 1 || (int64_t)chs.size() >= cap || (int64_t)hsrc.size() + H > cap * GatherShape<1>::REG)
-            return LBMP_OK;  // does not fit the reserved tables: variant not offered
-        for (size_t e = 0, q = 0; e < halo.size(); ++e) {
-            while (q + 1 < hq.size() && hq[q + 1] <= halo[e]) ++q;
-            pos[halo[e]] = (int32_t)(4 * (Cq + (int64_t)q) + (halo[e] - hq[q]));
-        }
-        for (int64_t i = base; i < base + C; ++i)
-            for (int k = 0; k < NL; ++k) {
-                const int64_t m = from(gnode[i], k);
-                int32_t sl = (int32_t)ZS;
-                if (cls[m]) {
-                    const int32_t j = gidx[m];
-                    sl = (j >= base && j < base + C) ? (int32_t)(j - base) : pos[j];
-                }
-                nbr[(size_t)k * NF + i] = (uint16_t)sl;
-            }
-        for (const int32_t h : halo) pos[h] = -1;
-        chs.push_back(make_int4((int)base, (int)C, (int)hsrc.size(), (int)H));
-        hsrc.insert(hsrc.end(), hq.begin(), hq.end());
-        base += C;
-    }
-    const int64_t nch = (int64_t)chs.size();
-    LBMP_HIP(hipMemcpyAsync(g.gidx, gidx.data(), N * 4, hipMemcpyHostToDevice, s));
-    LBMP_HIP(hipMemcpyAsync(g.gnode, gnode.data(), NF * 4, hipMemcpyHostToDevice, s));
-    LBMP_HIP(hipMemcpyAsync(g.gaslot, gaslot.data(), NF * 4, hipMemcpyHostToDevice, s));
-    LBMP_HIP(hipMemcpyAsync(g.gch, chs.data(), nch * sizeof(int4), hipMemcpyHostToDevice, s));
-    if (!hsrc.empty()) LBMP_HIP(hipMemcpyAsync(g.ghsrc, hsrc.data(), hsrc.size() * 4, hipMemcpyHostToDevice, s));
-    LBMP_HIP(hipMemcpyAsync(g.gnbr, nbr.data(), nbr.size() * 2, hipMemcpyHostToDevice, s));
-    LBMP_HIP(hipMemcpyAsync(g.aperm, aperm.data(), aperm.size() * 4, hipMemcpyHostToDevice, s));
-    LBMP_HIP(hipStreamSynchronize(s));
-    g.nch = nch;
-    g.gidx_h = std::move(gidx);
-    g.aperm_h = std::move(aperm);
-    g.gather_ok = true;
-    return LBMP_OK;
-}
-
 // The state at t = 1 lives in the odd buffer X1; X0 starts at zero. In uptake
 // mode X1 holds the start tau = 0: density 1/N_F on every fluid node, first
 // moments and adsorbed densities zero.
@@ -3103,25 +3053,22 @@ lbmp_status init_state(lbmp_mp* h, GeomHost& g, hipStream_t s) {
     return LBMP_OK;
 }
 
+// The state and the final layout of geometry g's link tables, from what
+// build_links has left in the scratch.
 template <typename T>
-lbmp_status setup_all(lbmp_mp* h, hipStream_t s) {
-    double r[SETUP_RED];
-    for (auto& g : h->g) {
-        lbmp_status st = build_links<T>(h, g, s, r);
-        if (st != LBMP_OK) return st;
-        st = species_constants<T>(h, g, r, s);
-        if (st != LBMP_OK) return st;
-        st = build_fidx(g, s);
-        if (st != LBMP_OK) return st;
-        if (h->prec == LBMP_FP32) {
-            st = build_gather(g, s);
-            if (st != LBMP_OK) return st;
-        }
-        LBMP_HIP(hipMemsetAsync(g.X0, 0, (size_t)g.S * 4 * g.N * sizeof(T), s));
-        LBMP_HIP(hipMemsetAsync(g.X1, 0, (size_t)g.S * 4 * g.N * sizeof(T), s));
-        LBMP_HIP(hipMemsetAsync(g.Xa, 0, (size_t)g.S * 4 * std::max<int64_t>(g.NI, 1) * sizeof(T), s));
-    }
-    std::vector<int32_t> work;
+lbmp_status finish_geom(lbmp_mp* h, GeomHost& g, hipStream_t s) {
+    lbmp_status st = init_state<T>(h, g, s);
+    if (st == LBMP_OK && compact_fields(h)) st = compact_links<T>(h, g, s);
+    return st;
+}
+
+template <typename T>
+lbmp_status setup_steps(lbmp_mp* h, hipStream_t s) {
+    bool chosen = false;
+    for (auto& g : h->g) rank_fluid(g.flow, g.fidx, g.fnode, s);
+    lbmp_status st = choose_tile(h, &chosen);
+    if (st != LBMP_OK) return st;
+    std::vector<int32_t>& work = h->work_h;
     for (int gi = 0; gi < h->ngeom; ++gi)
         for (int sp = 0; sp < h->g[gi].S; ++sp) {
             work.push_back(gi);
@@ -3129,28 +3076,50 @@ lbmp_status setup_all(lbmp_mp* h, hipStream_t s) {
         }
     LBMP_HIP(hipMemcpyAsync(h->work, work.data(), work.size() * 4, hipMemcpyHostToDevice, s));
     // LBMP_MASS_DRIFT_MAX overrides the watchdog threshold (tests force it)
-    double drift_max = LBMP_MASS_DRIFT_MAX;
-    if (const char* e = getenv("LBMP_MASS_DRIFT_MAX")) drift_max = atof(e);
-    h->drift_max = drift_max;
-    Ctl c0{1, h->tmax, 0u, INT64_MAX, h->uptake ? 1.0 : 0.0, drift_max};
-    LBMP_HIP(hipMemcpyAsync(h->ctl, &c0, sizeof c0, hipMemcpyHostToDevice, s));
-    LBMP_HIP(hipStreamSynchronize(s));
-    lbmp_status st = autotune(h);
+    h->drift_max = LBMP_MASS_DRIFT_MAX;
+    if (const char* e = getenv("LBMP_MASS_DRIFT_MAX")) h->drift_max = atof(e);
+    h->ctl0 = {1, h->tmax, 0u, INT64_MAX, h->uptake ? 1.0 : 0.0, h->drift_max};
+    LBMP_HIP(hipMemcpyAsync(h->ctl, &h->ctl0, sizeof h->ctl0, hipMemcpyHostToDevice, s));
+    double r[SETUP_RED];
+    for (auto& g : h->g) {
+        st = build_links<T>(h, g, s, r);
+        if (st != LBMP_OK) return st;
+        st = species_constants<T>(h, g, r, s);
+        if (st != LBMP_OK) return st;
+        if (chosen) {
+            st = finish_geom<T>(h, g, s);
+            if (st != LBMP_OK) return st;
+            continue;
+        }
+        LBMP_HIP(hipMemsetAsync(g.X0, 0, (size_t)g.S * 4 * g.N * sizeof(T), s));
+        LBMP_HIP(hipMemsetAsync(g.X1, 0, (size_t)g.S * 4 * g.N * sizeof(T), s));
+        LBMP_HIP(hipMemsetAsync(g.Xa, 0, (size_t)g.S * 4 * std::max<int64_t>(g.NI, 1) * sizeof(T), s));
+    }
+    if (chosen) return LBMP_OK;
+    st = autotune(h);
     if (st != LBMP_OK) return st;
     // tuning advanced the device time and wrote the buffers: start over
-    LBMP_HIP(hipMemcpyAsync(h->ctl, &c0, sizeof c0, hipMemcpyHostToDevice, s));
+    LBMP_HIP(hipMemcpyAsync(h->ctl, &h->ctl0, sizeof h->ctl0, hipMemcpyHostToDevice, s));
     for (auto& g : h->g) {
         st = build_links<T>(h, g, s, nullptr);
         if (st != LBMP_OK) return st;
-        st = init_state<T>(h, g, s);
+        st = finish_geom<T>(h, g, s);
         if (st != LBMP_OK) return st;
-        if (compact_fields(h)) {
-            st = compact_links<T>(h, g, s);
-            if (st != LBMP_OK) return st;
-        }
     }
-    LBMP_HIP(hipStreamSynchronize(s));
     return LBMP_OK;
+}
+
+template <typename T>
+lbmp_status setup_all(lbmp_mp* h, hipStream_t s) {
+    const lbmp_status st = setup_steps<T>(h, s);
+    // copies from the handle's host arrays are done, on a failure too
+    const hipError_t e = hipStreamSynchronize(s);
+    if (st == LBMP_OK) LBMP_HIP(e);
+    for (auto& g : h->g) {
+        g.up64 = std::vector<double>();
+        g.upT = std::vector<char>();
+    }
+    return st;
 }
 
 lbmp_status check_mp(const lbmp_mp* h) {
@@ -3520,14 +3489,22 @@ lbmp_status ckp_maps(const lbmp_mp* h, const GeomHost& g, CkpMaps& m) {
     std::vector<int8_t> cls(g.N);
     LBMP_HIP(hipMemcpyAsync(cls.data(), g.flow->d.cls, g.N, hipMemcpyDeviceToHost, h->stream));
     LBMP_HIP(hipStreamSynchronize(h->stream));
-    const std::vector<int32_t>* map = !compact_fields(h) ? nullptr : (h->variant == 8 ? &g.gidx_h : &g.fidx_h);
+    std::vector<int32_t> map, aperm;
+    if (compact_fields(h)) {
+        map.resize(g.N);
+        LBMP_HIP(hipMemcpy(map.data(), cidx(h, g), g.N * 4, hipMemcpyDeviceToHost));
+    }
+    if (h->variant == 8 && g.NI > 0) {
+        aperm.resize(g.NI);
+        LBMP_HIP(hipMemcpy(aperm.data(), g.aperm, g.NI * 4, hipMemcpyDeviceToHost));
+    }
     m.node.clear();
     m.node.reserve(g.nf);
     for (int64_t n = 0; n < g.N; ++n)
-        if (cls[n]) m.node.push_back(map ? (int64_t)(*map)[n] : n);
+        if (cls[n]) m.node.push_back(map.empty() ? n : (int64_t)map[n]);
     if ((int64_t)m.node.size() != g.nf) return fail(LBMP_ESTATE, "fluid node count differs from the set-up");
     m.slot.resize(g.NI);
-    for (int64_t i = 0; i < g.NI; ++i) m.slot[i] = h->variant == 8 ? g.aperm_h[i] : i;
+    for (int64_t i = 0; i < g.NI; ++i) m.slot[i] = aperm.empty() ? i : aperm[i];
     return LBMP_OK;
 }
 
