@@ -29,8 +29,6 @@ constexpr int PAD_IN = 32;   // 6 features padded
 constexpr int PAD_OUT = 32;  // 1 output padded
 constexpr int NFEAT = 6;
 
-__host__ __device__ constexpr int lin(int l) { return l == 0 ? PAD_IN : WIDTH; }
-__host__ __device__ constexpr int lout(int l) { return l == NLAYER - 1 ? PAD_OUT : WIDTH; }
 __host__ __device__ constexpr int tin(int l) { return l == 0 ? NFEAT : WIDTH; }   // true fan-in
 __host__ __device__ constexpr int tout(int l) { return l == NLAYER - 1 ? 1 : WIDTH; }
 
@@ -43,16 +41,24 @@ __host__ __device__ constexpr int woff(int l) {
 __host__ __device__ constexpr int boff(int l) { return woff(l) + tout(l) * tin(l); }
 constexpr int NPAR = woff(NLAYER);
 static_assert(boff(0) % 4 == 0 && boff(1) % 4 == 0 && boff(2) % 4 == 0, "hidden biases are read four at a time");
+static_assert(boff(2) - boff(1) == boff(1) - boff(0), "hidden biases at one stride");
+
+// MFMA operands are stored fragment by fragment: a 32 x 16 piece (32 rows, 16
+// consecutive k) is 64 runs of 8 values, run (k / 8) 32 + row, so a wave's
+// operand load is one contiguous kilobyte. (Row-major, a load touches 32
+// lines for 32 bytes each, four loads share a line, and between them the
+// block's other loads have evicted it: a layer's weights crossed from the L2
+// four times, 3.4 us of a CU's bandwidth.)
+// Offset of element (row, k) of a matrix with ks fragments of k per row tile.
+__host__ __device__ constexpr int frag(int row, int k, int ks) {
+    return ((row / 32 * ks + k / 16) * 64 + k % 16 / 8 * 32 + row % 32) * 8 + k % 8;
+}
 
 // The logistic function through the hardware reciprocal (v_rcp_f32, 1 ulp):
 // an IEEE division would cost ten instructions per value, and the epilogues
 // are rounded to bf16 anyway.
 __device__ __forceinline__ float sigm(float z) { return __builtin_amdgcn_rcpf(1.0f + __expf(-z)); }
 __device__ __forceinline__ float silu(float z) { return z * sigm(z); }
-__device__ __forceinline__ float silu_grad(float z) {
-    const float s = sigm(z);
-    return s * (1.0f + z * (1.0f - s));
-}
 
 // Fused inference: one block (8 waves) per FS samples runs all four layers
 // with the activations in LDS (one buffer: a layer's products read it, and
@@ -93,7 +99,7 @@ k_mlp_forward(const float* __restrict__ x, int64_t n, const float* __restrict__ 
         f32x16 acc[ST] = {};
 #pragma unroll 2
         for (int k0 = 0; k0 < K; k0 += 16) {
-            const bf16x8 w = *reinterpret_cast<const bf16x8*>(W + (size_t)(n0 + r) * K + k0 + kh);
+            const bf16x8 w = *reinterpret_cast<const bf16x8*>(W + frag(n0, k0, K / 16) + lane * 8);
             bf16x8 a[ST];
 #pragma unroll
             for (int j = 0; j < ST; ++j) a[j] = *reinterpret_cast<const bf16x8*>(act + (32 * j + r) * APITCH + k0 + kh);
@@ -129,7 +135,7 @@ k_mlp_forward(const float* __restrict__ x, int64_t n, const float* __restrict__ 
         f32x16 acc = {};
 #pragma unroll 4
         for (int k0 = 0; k0 < WIDTH; k0 += 16) {
-            const bf16x8 w = *reinterpret_cast<const bf16x8*>(W3 + (size_t)r * WIDTH + k0 + kh);
+            const bf16x8 w = *reinterpret_cast<const bf16x8*>(W3 + frag(0, k0, WIDTH / 16) + lane * 8);
             const bf16x8 a = *reinterpret_cast<const bf16x8*>(act + (32 * wave + r) * APITCH + k0 + kh);
             acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, a, acc, 0, 0, 0);
         }
@@ -144,50 +150,68 @@ constexpr int GSPLIT_MAX = 32;
 constexpr int GP1 = WIDTH * PAD_IN, GP2 = GP1 + WIDTH * WIDTH, GP3 = GP2 + WIDTH * WIDTH, GP = GP3 + WIDTH;
 constexpr int GPB = 3 * WIDTH + 1;
 
+constexpr int SQ = WIDTH * WIDTH;
+
 struct TrainBufs {
-    const float* norm;                    // [6] mean, [6] std, y_mean, y_std
-    const float* P;                       // packed parameters
-    const __bf16 *W0, *W1, *W2, *W3;      // [out][in], padded
-    const __bf16 *WT1, *WT2;              // [in][out]
-    // batch-major rows [feature][B]: inputs, activations, gradients by pre-activation
-    __bf16 *xT, *AT[3], *dZT[3], *dYT;
-    float* sq;                            // [B] squared errors
+    const float* norm;      // [6] mean, [6] std, y_mean, y_std
+    const float* P;         // packed parameters
+    const __bf16 *W0, *W3;  // fragments of [out][in], padded
+    const __bf16* Wsq;      // the square layers: W_2, W_3 [out][in], then W_3, W_2 [in][out]
+    // fragments of [feature][B]: inputs (padded), activations and gradients by
+    // pre-activation of the hidden layers (lstride apart); output gradient [B]
+    __bf16 *xT, *AT, *dZT, *dYT;
+    size_t lstride;
+    float* sq;              // [B] squared errors
 };
 
-// Forward and backward pass of 32 ST rows (x[idx], y[idx]; idx null: in order)
-// in one block of 8 waves: wave w owns features 32 w .. 32 w + 31 of every
-// layer, as the transposed product (weights first), so its pre-activations
-// stay in the accumulators' registers from the forward to the backward pass.
-// Activations and gradients pass between the waves through LDS and leave,
-// batch-major, as the operands of the weight gradients. The weight fragments
-// of a layer are loaded while the layer before computes. Bound by the chain
-// of six 256-wide layers (an MFMA chain, an epilogue and a barrier each);
-// as 12 launches (gather, GEMMs, loss) it took 75 us at batch 1,024.
-template <int ST>
+// Barrier for data passed through LDS: waits for this wave's LDS operations
+// only. __syncthreads() also waits for every global store and load in flight,
+// which nothing in the block depends on.
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0), vmcnt and expcnt at their maxima
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// Forward and backward pass of 32 rows (x[idx], y[idx]; idx null: in order) in
+// one block of 8 waves: wave w owns features 32 w .. 32 w + 31 of every layer,
+// as the transposed product (weights first). Activations, gradients and
+// silu'(Z) pass through LDS; activations and gradients also leave,
+// batch-major, as the operands of the weight gradients. A layer's weight
+// fragments are loaded while the epilogue before it runs.
+// At batch 1,024 the 32 blocks run once: bound by the chain of six layers
+// (weights from the L2, MFMA chain, epilogue, barrier).
+constexpr int RB = 32;           // rows per block
+constexpr int ZP = WIDTH + 4;    // floats per row of silu'(Z)
+
 __global__ void __launch_bounds__(512) k_train_rows(const float* __restrict__ x, const float* __restrict__ y,
                                                     const int32_t* __restrict__ idx, int B, TrainBufs T) {
-    constexpr int RB = 32 * ST, KS = WIDTH / 16;
+    constexpr int KS = WIDTH / 16;
     __shared__ __align__(16) __bf16 act[2][RB * APITCH];
+    __shared__ __align__(16) float G[3][RB * ZP];  // silu'(Z) of the hidden layers
     __shared__ __align__(16) __bf16 w3[WIDTH];
     __shared__ float ty[RB], dy[RB];
     const int r0 = blockIdx.x * RB;
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int r = lane & 31, hi = lane >> 5, kh = hi * 8, n0 = 32 * wave;
-    auto load_w = [&](const __bf16* __restrict__ W, bf16x8 (&w)[KS]) {
+    bf16x8 w[KS], w0[2];
+    auto load_w = [&](int m) {  // square matrix m
+        const __bf16* const W = T.Wsq + (size_t)m * SQ + frag(n0, 0, KS) + lane * 8;
 #pragma unroll
-        for (int k = 0; k < KS; ++k) w[k] = *reinterpret_cast<const bf16x8*>(W + (n0 + r) * WIDTH + 16 * k + kh);
+        for (int k = 0; k < KS; ++k) w[k] = *reinterpret_cast<const bf16x8*>(W + 512 * k);
     };
-    bf16x8 wa[KS], wb[KS], w0[2];
 #pragma unroll
-    for (int k = 0; k < 2; ++k) w0[k] = *reinterpret_cast<const bf16x8*>(T.W0 + (n0 + r) * PAD_IN + 16 * k + kh);
-    load_w(T.W1, wa);
+    for (int k = 0; k < 2; ++k) w0[k] = *reinterpret_cast<const bf16x8*>(T.W0 + frag(n0, 16 * k, 2) + lane * 8);
+    load_w(0);
+#pragma unroll 1
     for (int i = t; i < RB * PAD_IN; i += 512) {
         const int row = i / PAD_IN, c = i % PAD_IN;
         __bf16 v = (__bf16)0.0f;
         if (c < NFEAT) {
             const int64_t s = idx ? idx[r0 + row] : r0 + row;
             v = (__bf16)((x[s * NFEAT + c] - T.norm[c]) / T.norm[6 + c]);
-            T.xT[(size_t)c * B + r0 + row] = v;
+            T.xT[frag(c, r0 + row, 0)] = v;  // one row tile
         }
         act[0][row * APITCH + c] = v;
     }
@@ -195,127 +219,110 @@ __global__ void __launch_bounds__(512) k_train_rows(const float* __restrict__ x,
         const int64_t s = idx ? idx[r0 + t] : r0 + t;
         ty[t] = (y[s] - T.norm[12]) / T.norm[13];
     }
-    if (t < WIDTH) w3[t] = T.W3[t];
-    __syncthreads();
-    float Z[3][ST][16];
-    f32x16 acc[ST];
-    auto product = [&](const bf16x8* w, int ks, const __bf16* in) {
+    if (t < WIDTH) w3[t] = T.W3[frag(0, t, KS)];
+    lds_barrier();
+    f32x16 acc = {};
+    auto product = [&](const __bf16* in) {
+        acc = f32x16{};
 #pragma unroll
-        for (int j = 0; j < ST; ++j) acc[j] = f32x16{};
-#pragma unroll
-        for (int k = 0; k < KS; ++k) {
-            if (k >= ks) break;
-            if (k % 4 == 0) __builtin_amdgcn_sched_barrier(0);  // at most 4 steps' operands in flight: registers
-#pragma unroll
-            for (int j = 0; j < ST; ++j)
-                acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                    w[k], *reinterpret_cast<const bf16x8*>(in + (32 * j + r) * APITCH + 16 * k + kh), acc[j], 0, 0, 0);
-        }
+        for (int k = 0; k < KS; ++k)
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                w[k], *reinterpret_cast<const bf16x8*>(in + r * APITCH + 16 * k + kh), acc, 0, 0, 0);
     };
-    // element v of a lane's tile: feature n0 + 8 (v / 4) + 4 hi + v % 4, row 32 j + r
-    auto put = [&](int j, int g, const bf16x4& o, __bf16* lds, __bf16* __restrict__ out) {
-        const int fw = 8 * g + 4 * hi;  // feature within the wave's 32
-        *reinterpret_cast<bf16x4*>(lds + (32 * j + r) * APITCH + n0 + fw) = o;
-        // a scalar base per wave and 32-bit byte offsets from it (B up to 2^26)
-        char* const base = reinterpret_cast<char*>(out + (size_t)n0 * B + r0);
+    // element v of a lane's tile: feature n0 + 8 (v / 4) + 4 hi + v % 4, row r.
+    // Group g = v / 4 of the four is moved to elements 0 .. 3.
+    auto rotate = [&]() {
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-            *reinterpret_cast<__bf16*>(base + 2u * ((uint32_t)(fw + e) * (uint32_t)B + (uint32_t)(32 * j + r))) = o[e];
+        for (int v = 0; v < 12; ++v) acc[v] = acc[v + 4];
     };
-    auto hidden = [&](auto lc, __bf16* lds) {
-        constexpr int l = decltype(lc)::value;
+    auto put = [&](int fw, const bf16x4& o, __bf16* lds, __bf16* __restrict__ out) {
+        *reinterpret_cast<bf16x4*>(lds + r * APITCH + n0 + fw) = o;
+        // the wave's row tile, the block's two fragments of it
+        __bf16* const base = out + ((size_t)wave * (B / 16) + r0 / 16) * 512 + frag(fw, r, 2);
 #pragma unroll
+        for (int e = 0; e < 4; ++e) base[8 * e] = o[e];
+    };
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+            w0[k], *reinterpret_cast<const bf16x8*>(act[0] + r * APITCH + 16 * k + kh), acc, 0, 0, 0);
+#pragma unroll 1
+    for (int l = 0; l < 3; ++l) {
+        __bf16* const to = act[(l & 1) ^ 1];
+        const float* const bias = T.P + boff(0) + l * (boff(1) - boff(0)) + n0 + 4 * hi;
+#pragma unroll 1
         for (int g = 0; g < 4; ++g) {
-            __builtin_amdgcn_sched_barrier(0);
-            const float4 bc = *reinterpret_cast<const float4*>(T.P + boff(l) + n0 + 8 * g + 4 * hi);
+            const float4 bc = *reinterpret_cast<const float4*>(bias + 8 * g);
             const float b4[4] = {bc.x, bc.y, bc.z, bc.w};
+            bf16x4 o;
+            float4 d;
+            float* const dp = reinterpret_cast<float*>(&d);
 #pragma unroll
-            for (int j = 0; j < ST; ++j) {
-                bf16x4 o;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float z = acc[j][4 * g + e] + b4[e];
-                    Z[l][j][4 * g + e] = z;
-                    o[e] = (__bf16)silu(z);
-                }
-                put(j, g, o, lds, T.AT[l]);
+            for (int e = 0; e < 4; ++e) {
+                const float z = acc[e] + b4[e], s = sigm(z);
+                o[e] = (__bf16)(z * s);
+                dp[e] = s * (1.0f + z * (1.0f - s));
             }
+            *reinterpret_cast<float4*>(&G[l][r * ZP + n0 + 8 * g + 4 * hi]) = d;
+            put(8 * g + 4 * hi, o, to, T.AT + l * T.lstride);
+            rotate();
         }
-    };
-    auto dhidden = [&](auto lc, __bf16* lds) {
-        constexpr int l = decltype(lc)::value;
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int j = 0; j < ST; ++j) {
-                bf16x4 o;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    // the output layer's gradient has one nonzero column
-                    const float c = l == 2 ? dy[32 * j + r] * (float)w3[n0 + 8 * g + 4 * hi + e] : acc[j][4 * g + e];
-                    float z = Z[l][j][4 * g + e];
-                    asm volatile("" : "+v"(z));  // its logistic is formed again, not kept since the forward pass
-                    o[e] = (__bf16)(c * silu_grad(z));
-                }
-                put(j, g, o, lds, T.dZT[l]);
-            }
-        }
-    };
-    // the next layer's fragments: into the other set while this layer's
-    // epilogue runs, or (ST = 2, whose pre-activations leave registers for one
-    // set) into the same one after it
-    auto ahead = [&](const __bf16* __restrict__ W, bf16x8 (&w)[KS]) { if constexpr (ST == 1) load_w(W, w); };
-    auto after = [&](const __bf16* __restrict__ W) { if constexpr (ST > 1) load_w(W, wa); };
-    bf16x8(&wc)[KS] = ST == 1 ? wb : wa;
-    product(w0, 2, act[0]);
-    ahead(T.W2, wb);
-    hidden(std::integral_constant<int, 0>(), act[1]);
-    __syncthreads();
-    product(wa, KS, act[1]);
-    hidden(std::integral_constant<int, 1>(), act[0]);
-    after(T.W2);
-    __syncthreads();
-    product(wc, KS, act[0]);
-    hidden(std::integral_constant<int, 2>(), act[1]);
-    __syncthreads();
-    load_w(T.WT2, wa);
-    // output layer and loss: wave w the rows 32 w .. 32 w + 31, feature 0 in element 0 of lanes 0 .. 31
-    if (wave < ST) {
-        f32x16 o = {};
-#pragma unroll
-        for (int k = 0; k < KS; ++k) {
-            if (k % 4 == 0) __builtin_amdgcn_sched_barrier(0);
-            bf16x8 w{};
-            if (r == 0) w = *reinterpret_cast<const bf16x8*>(w3 + 16 * k + kh);
-            o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                w, *reinterpret_cast<const bf16x8*>(act[1] + (32 * wave + r) * APITCH + 16 * k + kh), o, 0, 0, 0);
-        }
-        if (lane < 32) {
-            const int b = 32 * wave + r;
-            const float e = (o[0] + T.P[boff(3)]) - ty[b];
-            const __bf16 d = (__bf16)(2.0f * e / (float)B);
-            dy[b] = (float)d;
-            T.dYT[r0 + b] = d;
-            T.sq[r0 + b] = e * e;
+        lds_barrier();
+        if (l < 2) {
+            product(to);
+            load_w(l + 1);  // W_3, then W_3 [in][out]
         }
     }
-    __syncthreads();
-    ahead(T.WT1, wb);
-    dhidden(std::integral_constant<int, 2>(), act[0]);
-    __syncthreads();
-    product(wa, KS, act[0]);
-    dhidden(std::integral_constant<int, 1>(), act[1]);
-    after(T.WT1);
-    __syncthreads();
-    product(wc, KS, act[1]);
-    dhidden(std::integral_constant<int, 0>(), act[0]);
+    // output layer and loss: feature 0 in element 0 of wave 0's lanes 0 .. 31
+    if (wave == 0) {
+        f32x16 o = {};
+#pragma unroll 4
+        for (int k = 0; k < KS; ++k) {
+            bf16x8 f{};
+            if (r == 0) f = *reinterpret_cast<const bf16x8*>(w3 + 16 * k + kh);
+            o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                f, *reinterpret_cast<const bf16x8*>(act[1] + r * APITCH + 16 * k + kh), o, 0, 0, 0);
+        }
+        if (lane < 32) {
+            const float e = (o[0] + T.P[boff(3)]) - ty[r];
+            const __bf16 d = (__bf16)(2.0f * e / (float)B);
+            dy[r] = (float)d;
+            T.dYT[r0 + r] = d;
+            T.sq[r0 + r] = e * e;
+        }
+    }
+    lds_barrier();
+    // the output layer's gradient has one nonzero column: dA_3 = dy w3
+    {
+        const float d = dy[r];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[v] = d * (float)w3[n0 + 8 * (v >> 2) + 4 * hi + (v & 3)];
+    }
+#pragma unroll 1
+    for (int l = 2;; --l) {
+        __bf16* const to = act[l & 1];
+#pragma unroll 1
+        for (int g = 0; g < 4; ++g) {
+            const float4 d = *reinterpret_cast<const float4*>(&G[l][r * ZP + n0 + 8 * g + 4 * hi]);
+            bf16x4 o;
+            o[0] = (__bf16)(acc[0] * d.x);
+            o[1] = (__bf16)(acc[1] * d.y);
+            o[2] = (__bf16)(acc[2] * d.z);
+            o[3] = (__bf16)(acc[3] * d.w);
+            put(8 * g + 4 * hi, o, to, T.dZT + l * T.lstride);
+            rotate();
+        }
+        if (l == 0) break;
+        lds_barrier();
+        product(to);
+        if (l == 2) load_w(3);  // W_2 [in][out]
+    }
 }
 
 // Parameter gradients over batch splits of kc rows. Wave job (split, tile):
 // one 32 x 32 tile of dW_l = dZ_l^T A_{l-1} over the split's rows, its partial
 // in P[split]; both operands are batch-major, so a lane's 8 rows are one
-// 16-byte load. The blocks behind them sum dZ for the biases, one thread per
+// 16-byte load, a wave's a contiguous kilobyte. The blocks behind them sum dZ for the biases, one thread per
 // (split, output): eight interleaved partial sums, then their sum in order.
 // Splitting K keeps the whole GPU busy where a 256 x 256 gradient has only 64
 // tiles; the partials are added in split order, so the result does not depend
@@ -332,61 +339,73 @@ __global__ void __launch_bounds__(256) k_train_grads(TrainBufs T, int B, int kc,
         const int job = blockIdx.x * 4 + wv, split = job / GTILES;
         int t = job % GTILES;
         const __bf16 *dz, *a;
-        int m0, n0, po, ld, na = WIDTH, nb = WIDTH;  // valid rows of the operands
+        int m0, n0, po, ld;
+        const int nk = B / 16;  // fragments per row tile
+        bool one = false;       // a single output row (the output layer)
         if (t < 2 * TN * TN) {
             const int l = t < TN * TN ? 1 : 2;
             t -= (l - 1) * TN * TN;
-            dz = T.dZT[l];
-            a = T.AT[l - 1];
             m0 = t / TN * 32;
             n0 = t % TN * 32;
+            dz = T.dZT + l * T.lstride;
+            a = T.AT + (l - 1) * T.lstride;
             po = l == 1 ? GP1 : GP2;
             ld = WIDTH;
         } else if ((t -= 2 * TN * TN) < TN) {
-            dz = T.dZT[0];
-            a = T.xT;
             m0 = 32 * t;
             n0 = 0;
+            dz = T.dZT;
+            a = T.xT;
             po = 0;
             ld = PAD_IN;
-            nb = NFEAT;
         } else {
-            dz = T.dYT;
-            a = T.AT[2];
             m0 = 0;
             n0 = 32 * (t - TN);
+            dz = T.dYT;
+            a = T.AT + 2 * T.lstride;
             po = GP3;
             ld = WIDTH;
-            na = 1;
+            one = true;
         }
         const int r = lane & 31, kh = (lane >> 5) * 8;
-        const bool va = m0 + r < na, vb = n0 + r < nb;
-        const __bf16* pa = dz + (size_t)(va ? m0 + r : 0) * B + split * kc + kh;
-        const __bf16* pb = a + (size_t)(vb ? n0 + r : 0) * B + split * kc + kh;
+        const __bf16* pb = a + ((size_t)(n0 / 32) * nk + split * kc / 16) * 512 + lane * 8;
+        const __bf16* pa = one ? dz + split * kc + kh : dz + ((size_t)(m0 / 32) * nk + split * kc / 16) * 512 + lane * 8;
         f32x16 acc = {};
+        if (one) {
 #pragma unroll 8
-        for (int k0 = 0; k0 < kc; k0 += 16) {
-            bf16x8 fa = *reinterpret_cast<const bf16x8*>(pa + k0), fb = *reinterpret_cast<const bf16x8*>(pb + k0);
-            if (!va) fa = bf16x8{};
-            if (!vb) fb = bf16x8{};
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, fb, acc, 0, 0, 0);
+            for (int k = 0; k < kc / 16; ++k) {
+                bf16x8 fa{};
+                if (r == 0) fa = *reinterpret_cast<const bf16x8*>(pa + 16 * k);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, *reinterpret_cast<const bf16x8*>(pb + 512 * k), acc, 0, 0, 0);
+            }
+        } else {
+#pragma unroll 8
+            for (int k = 0; k < kc / 16; ++k)
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(pa + 512 * k),
+                                                              *reinterpret_cast<const bf16x8*>(pb + 512 * k), acc, 0, 0, 0);
         }
         float* const out = P + (size_t)split * GP + po;
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int row = m0 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-            if (row < na) out[row * ld + n0 + r] = acc[v];
+            if (!one || row == 0) out[row * ld + n0 + r] = acc[v];
         }
         return;
     }
     const int id = ((int)blockIdx.x - wblocks) * 256 + (int)threadIdx.x;
     if (id >= GPB * splits) return;
     const int split = id / GPB, o = id % GPB;
-    const __bf16* p = (o < 3 * WIDTH ? T.dZT[o / WIDTH] + (size_t)(o % WIDTH) * B : T.dYT) + split * kc;
+    const __bf16* p = T.dYT + split * kc;
+    int half = 8, step = 16;  // from a run of 8 rows to the next, from a fragment to the next
+    if (o < 3 * WIDTH) {
+        p = T.dZT + o / WIDTH * T.lstride + ((size_t)(o % WIDTH / 32) * (B / 16) + split * kc / 16) * 512 + o % 32 * 8;
+        half = 256;
+        step = 512;
+    }
     float s[8] = {};
-#pragma unroll 4
-    for (int b = 0; b < kc; b += 8) {
-        const bf16x8 v = *reinterpret_cast<const bf16x8*>(p + b);
+#pragma unroll 8
+    for (int b = 0; b < kc / 8; ++b) {
+        const bf16x8 v = *reinterpret_cast<const bf16x8*>(p + (b >> 1) * step + (b & 1) * half);
 #pragma unroll
         for (int g = 0; g < 8; ++g) s[g] += (float)v[g];
     }
@@ -405,13 +424,18 @@ __device__ __forceinline__ void locate(int i, int& l, int& o, int& c) {
     c = k < nw ? k % in : -1;
 }
 
-struct Copies {  // bf16 copies of the weights
-    __bf16 *W[NLAYER], *WT[NLAYER];  // WT of the two square layers
+struct Copies {  // bf16 copies of the weights, as TrainBufs holds them
+    __bf16 *W0, *W3, *Wsq;
 };
 __device__ __forceinline__ void copy_bf16(const Copies& K, int l, int o, int c, float w) {
     if (c < 0) return;
-    K.W[l][o * (l == 0 ? PAD_IN : WIDTH) + c] = (__bf16)w;
-    if (l == 1 || l == 2) K.WT[l][c * WIDTH + o] = (__bf16)w;
+    const __bf16 b = (__bf16)w;
+    if (l == 0) K.W0[frag(o, c, 2)] = b;
+    else if (l == 3) K.W3[frag(0, c, WIDTH / 16)] = b;
+    else {
+        K.Wsq[(l - 1) * SQ + frag(o, c, WIDTH / 16)] = b;
+        K.Wsq[(4 - l) * SQ + frag(c, o, WIDTH / 16)] = b;
+    }
 }
 __global__ void k_copies(const float* __restrict__ P, Copies K) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -488,7 +512,7 @@ struct lbmp_sg {
     float *P, *m, *v, *G;       // packed parameters, Adam moments, gradients (sg_gradients)
     float* norm;                // [6] mean, [6] std, y_mean, y_std
     lbmp::mlp::Copies K;        // bf16 weights
-    __bf16 *xT, *AT[3], *dZT[3], *dYT;  // a batch's rows, batch-major
+    __bf16 *xT, *AT, *dZT, *dYT;  // a batch's rows, batch-major
     float* sq;                  // per-row squared errors [bmax]
     float* loss;                // [1]
     float* gsplit;              // [GSPLIT_MAX][GP] weight-gradient partials over batch splits
@@ -503,17 +527,14 @@ static void carve_sg(lbmp_sg* h, Carver& c) {
     h->m = c.take<float>(NPAR);
     h->v = c.take<float>(NPAR);
     h->G = c.take<float>(NPAR);
-    for (int l = 0; l < NLAYER; ++l) {
-        h->K.W[l] = c.take<__bf16>((size_t)lout(l) * lin(l));
-        h->K.WT[l] = l == 1 || l == 2 ? c.take<__bf16>((size_t)lout(l) * lin(l)) : nullptr;
-    }
+    h->K.W0 = c.take<__bf16>(WIDTH * PAD_IN);
+    h->K.W3 = c.take<__bf16>(PAD_OUT * WIDTH);
+    h->K.Wsq = c.take<__bf16>(4 * SQ);
     h->norm = c.take<float>(16);
     const size_t B = (size_t)h->bmax;
-    h->xT = c.take<__bf16>(B * NFEAT);
-    for (int l = 0; l < 3; ++l) {
-        h->AT[l] = c.take<__bf16>(B * WIDTH);
-        h->dZT[l] = c.take<__bf16>(B * WIDTH);
-    }
+    h->xT = c.take<__bf16>(B * PAD_IN);  // columns past the features stay zero
+    h->AT = c.take<__bf16>(3 * B * WIDTH);
+    h->dZT = c.take<__bf16>(3 * B * WIDTH);
     h->dYT = c.take<__bf16>(B);
     h->sq = c.take<float>(B);
     h->loss = c.take<float>(4);
@@ -531,14 +552,12 @@ static int grad_splits(int B) {
     return splits;
 }
 
-// Partial gradients of a batch: 32 rows per block while the blocks leave CUs
-// free, 64 (which halve the weight fragments read per row) from 512 blocks on.
+// Partial gradients of a batch.
 static void gradients(lbmp_sg* h, const float* x, const float* y, const int32_t* idx, int B) {
     hipStream_t s = h->stream;
-    const TrainBufs T{h->norm, h->P, h->K.W[0], h->K.W[1], h->K.W[2], h->K.W[3], h->K.WT[1], h->K.WT[2], h->xT,
-                      {h->AT[0], h->AT[1], h->AT[2]}, {h->dZT[0], h->dZT[1], h->dZT[2]}, h->dYT, h->sq};
-    if (B % 64 == 0 && B >= 512 * 32) k_train_rows<2><<<(unsigned)(B / 64), 512, 0, s>>>(x, y, idx, B, T);
-    else k_train_rows<1><<<(unsigned)(B / 32), 512, 0, s>>>(x, y, idx, B, T);
+    const TrainBufs T{h->norm, h->P, h->K.W0, h->K.W3, h->K.Wsq, h->xT, h->AT, h->dZT, h->dYT,
+                      (size_t)h->bmax * WIDTH, h->sq};
+    k_train_rows<<<(unsigned)(B / RB), 512, 0, s>>>(x, y, idx, B, T);
     const int splits = grad_splits(B);
     const unsigned nb = (unsigned)(GTILES / 4 * splits + (GPB * splits + 255) / 256);
     k_train_grads<<<nb, 256, 0, s>>>(T, B, B / splits, splits, h->gsplit, h->bsplit);
@@ -719,8 +738,8 @@ extern "C" lbmp_status sg_predict(lbmp_sg* h, const float* x_dev, int64_t n, flo
     hipStream_t s = h->stream;
     if (n > 0) {
         k_mlp_forward<<<(unsigned)((n + FS - 1) / FS), 64 * FWAVES, 0, s>>>(
-            x_dev, n, h->norm, h->K.W[0], h->P + boff(0), h->K.W[1], h->P + boff(1), h->K.W[2], h->P + boff(2),
-            h->K.W[3], h->P + boff(3), y_dev);
+            x_dev, n, h->norm, h->K.W0, h->P + boff(0), h->K.Wsq, h->P + boff(1), h->K.Wsq + SQ, h->P + boff(2),
+            h->K.W3, h->P + boff(3), y_dev);
     }
     LBMP_HIP(hipGetLastError());
     return LBMP_OK;

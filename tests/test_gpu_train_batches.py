@@ -1,6 +1,6 @@
 """Fused training pass at the edges of its batch shapes: one block of rows, an
-odd number of 32-row blocks, splits that do not divide evenly, the 64-row
-blocks of large batches and the 32-row ones beside them. Gradients against the
+odd number of 32-row blocks, splits that do not divide evenly, batches of
+more blocks than CUs. Gradients against the
 FP64 network (bf16 operands carry 2^-9 each; norm-wise errors of a few of
 those, independent of the batch: 2e-2), rows through an index list against
 the same rows in order (bitwise)."""
