@@ -212,12 +212,13 @@ lbmp_status validate_geometry(const lbmp_geometry* g) {
     if (g->iface_nbhd != 0 && g->iface_nbhd != 6 && g->iface_nbhd != 18)
         return fail(LBMP_EINVAL, "iface_nbhd must be 0, 6 or 18");
     const int n[3] = {g->nx, g->ny, g->nz};
-    bool any_fluid = false;
+    uint8_t all = 1, any = 0;
     for (int64_t i = 0; i < N; ++i) {
-        if (g->solid[i] > 1) return fail(LBMP_EINVAL, "solid mask values must be 0 or 1");
-        any_fluid |= g->solid[i] == 0;
+        all &= g->solid[i];
+        any |= g->solid[i];
     }
-    if (!any_fluid) return fail(LBMP_EINVAL, "geometry has no fluid node");
+    if (any > 1) return fail(LBMP_EINVAL, "solid mask values must be 0 or 1");
+    if (all) return fail(LBMP_EINVAL, "geometry has no fluid node");
     for (int d = 0; d < 3; ++d) {
         if (g->periodic[d]) continue;
         for (int side = 0; side < 2; ++side) {

@@ -1,0 +1,79 @@
+"""The flow solve's three forms by size (whole solve in one block, steps
+through the pull table, steps through the index map) do the same arithmetic:
+a lattice and its periodic repetitions, one in each form, must give bitwise
+the same velocities, steps and residual; the one-block form also where it can
+go wrong: block sizes, check intervals shorter than the velocity history,
+launches of limited length (against the FP64 oracle)."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1303_2470_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def lb():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1303_2470_amd import lbmp
+    lbmp.load_library()
+    return lbmp
+
+
+@pytest.mark.parametrize("tau,tol,steps,ce", [(1.0, 1e-6, 3000, 100), (0.7, 0.0, 250, 3), (1.9, 1e-4, 2000, 1)])
+def test_repetitions_equal(lb, tau, tol, steps, ce):
+    m = inputs.random_mask(8, 6, 10, 0.3, seed=12)
+    force = [1e-5, -2e-6, 3e-6]
+    ref = None
+    for reps in ((1, 1, 1), (2, 2, 2), (10, 9, 8)):   # about 340, 2,700 and 242,000 fluid nodes
+        f = lb.lb_flow_solve(np.tile(m, reps), tau, force, tol, steps, check_every=ce, allow_unconverged=True)
+        u, got = f.velocity(), (f.steps, f.residual, f.converged)
+        f.free()
+        if ref is None:
+            ref = u, got
+            continue
+        assert got == ref[1], reps
+        assert np.array_equal(u, np.tile(ref[0], (1,) + reps)), reps
+
+
+def _medium(nf, seed):
+    nx, ny = 13, 7
+    nz = max(2, -(-int(1.3 * nf) // (nx * ny)))
+    m = np.ones(nx * ny * nz, dtype=np.uint8)
+    m[np.random.default_rng(seed).permutation(m.size)[:nf]] = 0
+    return m.reshape(nz, ny, nx)
+
+
+@pytest.mark.parametrize("nf", [1, 64, 65, 128, 129, 256, 257, 512, 513, 1024])
+@pytest.mark.parametrize("ce", [0, 2])
+def test_block_sizes_equal_steps(lb, nf, ce):
+    """The one-block form at the edges of its block sizes against the step
+    kernels on a repetition along x of more nodes than it takes: bitwise."""
+    m, force = _medium(nf, nf), [2e-6, 1e-6, -1e-6]
+    reps = (1, 1, 1100 // nf + 1)
+    for steps in (1, 2, 130):
+        got = []
+        for mask in (m, np.tile(m, reps)):
+            f = lb.lb_flow_solve(mask, 0.9, force, 0.0, steps, check_every=ce, allow_unconverged=True)
+            got.append((f.velocity(), f.steps, f.residual, f.converged))
+            f.free()
+        assert got[0][1:] == got[1][1:] and got[0][1] == steps
+        assert np.array_equal(np.tile(got[0][0], (1,) + reps), got[1][0])
+
+
+def test_long_solves_cross_launches(lb):
+    """A solve of more steps than one launch takes, stopped by its step limit
+    and by its tolerance."""
+    m = inputs.slit_mask(1, 1, 60)
+    f = lb.lb_flow_solve(m, 1.0, [1e-7, 0, 0], 0.0, 20057, check_every=50, allow_unconverged=True)
+    ref = oracle.bgk(m, 1.0, [1e-7, 0, 0], 0.0, 20057)
+    assert f.steps == 20057
+    assert np.abs(f.velocity() - ref["u"]).max() < 1e-11 * np.abs(ref["u"]).max()
+    f.free()
+    f = lb.lb_flow_solve(m, 1.0, [1e-7, 0, 0], 1e-10, 400000)
+    ref = oracle.bgk(m, 1.0, [1e-7, 0, 0], 1e-10, 400000)
+    assert f.converged and f.steps == ref["steps"] and f.steps > 20000
+    f.free()
