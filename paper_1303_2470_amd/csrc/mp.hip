@@ -2321,6 +2321,10 @@ int64_t ntile_for(const lbmp_flow* f, int K, int variant) {
 int64_t setup_doubles(int64_t N) { return 24 * N + ((N + BLK - 1) / BLK) * SETUP_RED + SETUP_RED; }
 double* setup_bmu(double* base, int64_t N) { return base + 22 * N + ((N + BLK - 1) / BLK) * SETUP_RED + SETUP_RED; }
 
+// Values kept zero behind the last stored field: the gathered chunks' 16-byte
+// copies reach past it, and lanes without a node multiply what they find by 0.
+constexpr int64_t XPAD = 64;
+
 template <typename T>
 void carve_geom(GeomHost& g, Carver& c, int64_t tmax) {
     const int64_t N = g.N, NIa = std::max<int64_t>(g.NI, 1);
@@ -2329,8 +2333,8 @@ void carve_geom(GeomHost& g, Carver& c, int64_t tmax) {
     g.sig = c.take<double>(N);
     g.src = c.take<T>(N);
     g.a = c.take<T>(3 * N);
-    g.X0 = c.take<T>(S * 4 * N);
-    g.X1 = c.take<T>(S * 4 * N);
+    g.X0 = c.take<T>(S * 4 * N + XPAD);
+    g.X1 = c.take<T>(S * 4 * N + XPAD);
     g.Xa = c.take<T>(S * 4 * NIa);
     g.fidx = c.take<int32_t>(N);
     g.fnode = c.take<int32_t>(std::max<int64_t>(g.nf, 1));
@@ -3034,7 +3038,9 @@ lbmp_status init_state(lbmp_mp* h, GeomHost& g, hipStream_t s) {
     const int64_t N = g.N;
     double* b64 = h->setup_tmp + 18 * N;
     double* src64 = b64 + 3 * N;
-    LBMP_HIP(hipMemsetAsync(g.X0, 0, (size_t)g.S * 4 * N * sizeof(T), s));
+    const int64_t NC = compact_fields(h) ? g.nf : N;
+    LBMP_HIP(hipMemsetAsync(g.X0, 0, ((size_t)g.S * 4 * N + XPAD) * sizeof(T), s));
+    LBMP_HIP(hipMemsetAsync(static_cast<T*>(g.X1) + (size_t)g.S * 4 * NC, 0, XPAD * sizeof(T), s));
     if (h->uptake) {
         LBMP_HIP(hipMemsetAsync(g.X1, 0, (size_t)g.S * 4 * N * sizeof(T), s));
         LBMP_HIP(hipMemsetAsync(g.Xa, 0, (size_t)g.S * 4 * std::max<int64_t>(g.NI, 1) * sizeof(T), s));

@@ -60,3 +60,26 @@ def test_fields_equal_the_haloed_block(lb, monkeypatch, name, nh):
         assert np.array_equal(X, Xr) and np.array_equal(Xa, Xar)
     for k, v in got["4,2,2"][1].items():
         np.testing.assert_allclose(got["8,2,2"][1][k], v, rtol=1e-12, atol=1e-18)
+
+
+@pytest.mark.parametrize("tile", ["8,2,2", "4,2,2", "3,1,1", "0,1,2", "9,4,1"])
+@pytest.mark.parametrize("name", ["plane", "bulk 33x5x9", "random 48^3 0.95"])
+def test_workspace_content_does_not_matter(lb, monkeypatch, tile, name):
+    """The workspace the allocator hands out holds NaNs: the same series as
+    from a workspace of zeros."""
+    import torch
+    m = MASKS[name]()
+    fl = lb.lb_flow_from_velocity(m, inputs.random_velocity(m, 0.01, seed=9))
+    sp = {"D_b": 0.05, "k_a": [0.02, 0.3], "k_d": [0.01, 0.5]}
+    monkeypatch.setenv("LBMP_TILE", tile)
+    empty, got = torch.empty, []
+    for v in (0, 255):  # bytes of 255 are NaNs in FP32 and FP64
+        monkeypatch.setattr(torch, "empty", lambda *a, **k: empty(*a, **k).fill_(v))
+        mp = lb.mp_init(fl, sp, 32, 9)
+        monkeypatch.setattr(torch, "empty", empty)
+        lb.mp_step_n(mp, 9)
+        got.append((lb.mp_vacf(mp, 0), lb.mp_state(mp, 0, 1)))
+        mp.free()
+    for k in got[0][0]:
+        assert np.array_equal(got[0][0][k], got[1][0][k]), k
+    assert all(np.array_equal(a, b) for a, b in zip(got[0][1], got[1][1]))
