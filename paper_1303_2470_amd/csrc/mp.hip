@@ -90,7 +90,8 @@ struct GeomDev {
     const T* coef;             // [S][4]
     const T* prob;             // [S][2] = p_a, p_d
     const double* kc;          // [S][KC]: p_a, p_d, c_0..c_3 (coef), -V_0..-V_2, FP64
-    double* part;              // [S][ntile][NRED]
+    double* part;              // [2][S][ntile][NRED], the half by the parity of the time
+    int64_t pstride;           // S ntile NRED
     double* series;            // [Tmax][S][NRED], entry t-1 holds time t
 };
 
@@ -225,6 +226,104 @@ template <typename T> __device__ __forceinline__ T store_round(double v, uint32_
 template <> __device__ __forceinline__ float store_round<float>(double v, uint32_t r) { return sround(v, r); }
 template <> __device__ __forceinline__ double store_round<double>(double v, uint32_t) { return v; }
 
+// ------------------------------------------------------------------ series
+// The sums of a step are recorded by the launch of the next one: its last
+// blocks (past the step's own) reduce the partials the step before has left,
+// while the others propagate; after the last step of a call k_mp_tail does it
+// and moves the state time on. A reduction launched behind every step cost
+// 4.8 us on a single slit (of 19) and 11.6 us on the batched slits.
+// Lattices with many tiles go through two stages, one launch apart: chunks of
+// RCH tile partials, then the chunk sums.
+constexpr int RCH = 2048;
+
+struct Red {
+    const int32_t* work;  // (geometry, species) pairs
+    double* chunk;        // [2][nwork][nch][NRED] chunk sums, the half by the parity of the time
+    Ctl* ctl;
+    int nwork, nch;       // chunks per pair (1: none)
+    int n1, n2;           // blocks of the two stages in this launch
+    int dt;               // this launch's time less the state time
+};
+
+// Block b of the n1 + n2: a chunk (b < n1) of the partials of time t - 1, or
+// the sums of one pair at time t - 1 (t - 2 with chunks) into its series and
+// the watchdog. Fixed order: entries of a pair are one flat array, thread i
+// adds entries i, i + blockDim, ... (all of sum i % NRED) into eight
+// accumulators, and the threads of each sum are added by a fixed tree.
+template <typename T>
+__device__ __forceinline__ void series_block(const GeomDev<T>* __restrict__ geoms, const Red& R, int b) {
+    __shared__ double wsum[16][NRED];
+    const int tid = threadIdx.x, BD = blockDim.x, lane = tid & 63, wv = tid >> 6, nwv = BD / 64;
+    const int64_t t = R.ctl->t + R.dt;
+    const bool first = b < R.n1;
+    const int w = first ? b / R.nch : b - R.n1, c = first ? b % R.nch : 0;
+    const int64_t tau = first || R.nch == 1 ? t - 1 : t - 2;
+    const int gi = R.work[2 * w], s = R.work[2 * w + 1];
+    const GeomDev<T>& G = geoms[gi];
+    // global address space: flat loads would also count as LDS traffic and
+    // serialise the loads below
+    using gdp = const __attribute__((address_space(1))) double*;
+    double* const chunks = R.chunk + ((tau & 1) * R.nwork + w) * (int64_t)R.nch * NRED;
+    const double* src = chunks;
+    int64_t len = (int64_t)R.nch * NRED;
+    if (first || R.nch == 1) {
+        const int64_t i0 = (int64_t)c * RCH, i1 = R.nch == 1 ? G.ntile : min(G.ntile, i0 + RCH);
+        src = G.part + (tau & 1) * G.pstride + ((int64_t)s * G.ntile + i0) * NRED;
+        len = max((int64_t)0, i1 - i0) * NRED;
+    }
+    const gdp P = (gdp)src;
+    double acc[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) acc[u] = 0.0;
+    int64_t i = tid;
+    for (; i + 7 * BD < len; i += 8 * BD) {
+        double x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = P[i + u * BD];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc[u] += x[u];
+    }
+#pragma unroll
+    for (int u = 0; u < 7; ++u)
+        if (i + u * BD < len) acc[u] += P[i + u * BD];
+    double v = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
+    // lanes l, l ^ 8, l ^ 16, ... hold the same sum (l % 8)
+    v += __shfl_xor(v, 8, 64);
+    v += __shfl_xor(v, 16, 64);
+    v += __shfl_xor(v, 32, 64);
+    if (lane < NRED) wsum[wv][lane] = v;
+    __syncthreads();
+    if (tid < NRED) {
+        double r = wsum[0][tid];
+        for (int k = 1; k < nwv; ++k) r += wsum[k][tid];
+        if (first) {
+            chunks[c * NRED + tid] = r;
+        } else if (tau <= R.ctl->tmax) {
+            G.series[((tau - 1) * G.S + s) * NRED + tid] = r;
+            // total probability of the species (slots 3 and 7)
+            const double a = __shfl(r, 7, 64), m = __shfl(r, 3, 64);
+            if (tid == 0 && !(fabs(m + a - R.ctl->mass_ref) <= R.ctl->drift_max))
+                atomicMin(reinterpret_cast<unsigned long long*>(&R.ctl->bad_t), (unsigned long long)tau);
+        }
+    }
+}
+
+// What is left of a call's series, and the state time moved on by `advance`
+// steps by the last block to finish (every block has read it by then).
+template <typename T>
+__global__ void __launch_bounds__(BLK) k_mp_tail(const GeomDev<T>* __restrict__ geoms, Red R, int advance) {
+    series_block<T>(geoms, R, (int)blockIdx.x);
+    if (advance == 0) return;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        __threadfence();
+        if (atomicAdd(&R.ctl->done, 1u) == gridDim.x - 1) {
+            R.ctl->done = 0;
+            R.ctl->t += advance;
+        }
+    }
+}
+
 // One propagation step for every (geometry, species) pair. Loads and stores
 // are in the storage type T; the update itself is FP64 (an FMA chain for the
 // arrivals, the exact FP64 sum of the departures), rounded once on store —
@@ -232,7 +331,11 @@ template <> __device__ __forceinline__ double store_round<double>(double v, uint
 // step to step.
 template <typename T, int K>
 __global__ void __launch_bounds__(BLK) k_mp_step(const GeomDev<T>* __restrict__ geoms, int ngeom,
-                                                 int gsz, int64_t nblocks, const Ctl* __restrict__ ctl) {
+                                                 int gsz, int64_t nblocks, const Ctl* __restrict__ ctl, Red R) {
+    if ((int64_t)blockIdx.x >= nblocks) {
+        series_block<T>(geoms, R, (int)(blockIdx.x - nblocks));
+        return;
+    }
     __shared__ double lds[NRED * BLK];
     constexpr int E = (int)sizeof(T);
     T* const tag = nullptr;
@@ -268,7 +371,7 @@ __global__ void __launch_bounds__(BLK) k_mp_step(const GeomDev<T>* __restrict__ 
 #pragma unroll
         for (int c = 0; c < 4; ++c) offd[j][c] = inplane ? (zo + od[c]) * E : OOB;
     }
-    const int64_t t = ctl->t;
+    const int64_t t = ctl->t + R.dt;
     // per-node link data (FP64 in registers); inactive nodes read zeros
     bool act[K], isI[K];
     double pin[K][NL], sig[K], src[K], av[K][3];
@@ -362,7 +465,7 @@ __global__ void __launch_bounds__(BLK) k_mp_step(const GeomDev<T>* __restrict__ 
         double r;
         block_sum8(red, lds, r);
         if (threadIdx.x < NRED)
-            G.part[((int64_t)s * ntile + tile) * NRED + threadIdx.x] = r;
+            G.part[(t & 1) * G.pstride + ((int64_t)s * ntile + tile) * NRED + threadIdx.x] = r;
     }
 }
 
@@ -382,7 +485,11 @@ struct Box {
 
 template <typename T, int K>
 __global__ void __launch_bounds__(BLK) k_mp_step_box(const GeomDev<T>* __restrict__ geoms, int ngeom,
-                                                     int gsz, int64_t nblocks, const Ctl* __restrict__ ctl) {
+                                                     int gsz, int64_t nblocks, const Ctl* __restrict__ ctl, Red R) {
+    if ((int64_t)blockIdx.x >= nblocks) {
+        series_block<T>(geoms, R, (int)(blockIdx.x - nblocks));
+        return;
+    }
     using B = Box<K>;
     __shared__ T box[2][B::LOADS * BLK];
     __shared__ double lds[NRED * BLK];
@@ -417,7 +524,7 @@ __global__ void __launch_bounds__(BLK) k_mp_step_box(const GeomDev<T>* __restric
             goff[i] = OOB;
         }
     }
-    const int64_t t = ctl->t;
+    const int64_t t = ctl->t + R.dt;
     bool act[K], isI[K];
     int offn[K], offa[K];
     double pin[K][NL], sig[K], src[K], av[K][3];
@@ -520,7 +627,7 @@ __global__ void __launch_bounds__(BLK) k_mp_step_box(const GeomDev<T>* __restric
         if (q == 3) {
             double r;
             block_sum8(red, lds, r);   // synchronises the block
-            if (tid < NRED) G.part[((int64_t)s * ntile + tile) * NRED + tid] = r;
+            if (tid < NRED) G.part[(t & 1) * G.pstride + ((int64_t)s * ntile + tile) * NRED + tid] = r;
         } else {
             __syncthreads();
         }
@@ -542,10 +649,14 @@ struct Ring {
 
 template <typename T, int G>
 __global__ void __launch_bounds__(BLK) k_mp_march(const GeomDev<T>* __restrict__ geoms, int ngeom,
-                                                  int64_t nblocks, int zseg, const Ctl* __restrict__ ctl) {
+                                                  int64_t nblocks, int zseg, const Ctl* __restrict__ ctl, Red R) {
+    if ((int64_t)blockIdx.x >= nblocks) {
+        series_block<T>(geoms, R, (int)(blockIdx.x - nblocks));
+        return;
+    }
     constexpr int F = 4 * G;
-    using R = Ring<F>;
-    constexpr size_t RING_BYTES = 3 * F * R::PL * sizeof(T);
+    using RG = Ring<F>;
+    constexpr size_t RING_BYTES = 3 * F * RG::PL * sizeof(T);
     constexpr size_t RED_BYTES = NRED * BLK * sizeof(double);
     __shared__ __align__(16) char smem[RING_BYTES > RED_BYTES ? RING_BYTES : RED_BYTES];
     T* ring = reinterpret_cast<T*>(smem);  // [3][F][PL]
@@ -568,15 +679,15 @@ __global__ void __launch_bounds__(BLK) k_mp_march(const GeomDev<T>* __restrict__
     const int lx = tid % TX, ly = tid / TX;
     const int x = x0 + lx, y = y0 + ly;
     const bool inplane = x < nx && y < ny;
-    const int c0 = (ly + 1) * R::PX + (lx + 1);  // this thread's column in a haloed plane
+    const int c0 = (ly + 1) * RG::PX + (lx + 1);  // this thread's column in a haloed plane
     const int own = inplane ? y * nx + x : 0;
-    int poff[R::LOADS];
+    int poff[RG::LOADS];
 #pragma unroll
-    for (int i = 0; i < R::LOADS; ++i) {
+    for (int i = 0; i < RG::LOADS; ++i) {
         const int e = tid + i * BLK;
-        poff[i] = e < R::PL ? modp(y0 - 1 + e / R::PX, ny) * nx + modp(x0 - 1 + e % R::PX, nx) : -1;
+        poff[i] = e < RG::PL ? modp(y0 - 1 + e / RG::PX, ny) * nx + modp(x0 - 1 + e % RG::PX, nx) : -1;
     }
-    const int64_t t = ctl->t;
+    const int64_t t = ctl->t + R.dt;
     const T* Xin = (t & 1) ? Gm.X1 : Gm.X0;
     T* Xout = (t & 1) ? Gm.X0 : Gm.X1;
     const int s0 = grp * G, ns = min(G, Gm.S - s0);
@@ -601,21 +712,21 @@ __global__ void __launch_bounds__(BLK) k_mp_march(const GeomDev<T>* __restrict__
         pd[g] = (double)Gm.prob[2 * s + 1];
     }
 
-    auto fetch = [&](int pz, T (&reg)[F][R::LOADS]) {
+    auto fetch = [&](int pz, T (&reg)[F][RG::LOADS]) {
         const int zo = modp(pz, nz) * plane;
 #pragma unroll
         for (int f = 0; f < F; ++f)
 #pragma unroll
-            for (int i = 0; i < R::LOADS; ++i)
+            for (int i = 0; i < RG::LOADS; ++i)
                 reg[f][i] = bload(tag, rin, (f < 4 * ns && poff[i] >= 0) ? (zo + poff[i]) * E : OOB, f * N * E);
     };
-    auto stash = [&](int slot, const T (&reg)[F][R::LOADS]) {
+    auto stash = [&](int slot, const T (&reg)[F][RG::LOADS]) {
 #pragma unroll
         for (int f = 0; f < F; ++f)
 #pragma unroll
-            for (int i = 0; i < R::LOADS; ++i) {
+            for (int i = 0; i < RG::LOADS; ++i) {
                 const int e = tid + i * BLK;
-                if (e < R::PL) ring[(slot * F + f) * R::PL + e] = reg[f][i];
+                if (e < RG::PL) ring[(slot * F + f) * RG::PL + e] = reg[f][i];
             }
     };
     // node classes two planes ahead, link data and adsorbed values one plane ahead
@@ -648,7 +759,7 @@ __global__ void __launch_bounds__(BLK) k_mp_march(const GeomDev<T>* __restrict__
         return n >= 0 ? (int)__builtin_amdgcn_raw_buffer_load_b32(rslot, n * 4, 0, 0) : -1;
     };
 
-    T pre[F][R::LOADS];
+    T pre[F][RG::LOADS];
     fetch(zs - 1, pre);
     stash(0, pre);
     fetch(zs, pre);
@@ -695,13 +806,13 @@ __global__ void __launch_bounds__(BLK) k_mp_march(const GeomDev<T>* __restrict__
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int f = 4 * g + q;
-                const T* pm = ring + (sm * F + f) * R::PL;
-                const T* pc = ring + (sc * F + f) * R::PL;
-                const T* pp = ring + (sp * F + f) * R::PL;
+                const T* pm = ring + (sm * F + f) * RG::PL;
+                const T* pc = ring + (sc * F + f) * RG::PL;
+                const T* pp = ring + (sp * F + f) * RG::PL;
                 double acc0 = 0.0, acc1 = 0.0;
 #pragma unroll
                 for (int k = 0; k < NL; ++k) {
-                    const int o = c0 - lcy(k) * R::PX - lcx(k);
+                    const int o = c0 - lcy(k) * RG::PX - lcx(k);
                     const T v = lcz(k) > 0 ? pm[o] : (lcz(k) < 0 ? pp[o] : pc[o]);
                     if (k & 1) acc1 = __builtin_fma((double)v, pin[k], acc1);
                     else acc0 = __builtin_fma((double)v, pin[k], acc0);
@@ -740,7 +851,7 @@ __global__ void __launch_bounds__(BLK) k_mp_march(const GeomDev<T>* __restrict__
     for (int g = 0; g < G; ++g) {
         double r;
         block_sum8(red[g], lds, r);
-        if (tid < NRED && g < ns) Gm.part[((int64_t)(s0 + g) * ntile + tile) * NRED + tid] = r;
+        if (tid < NRED && g < ns) Gm.part[(t & 1) * Gm.pstride + ((int64_t)(s0 + g) * ntile + tile) * NRED + tid] = r;
     }
 }
 
@@ -877,7 +988,11 @@ struct Stages {
 // (porous media, where most lanes of a tile sit on solid nodes).
 template <int NH, bool ZX, bool FR, bool LC = false>
 __global__ void __launch_bounds__(NH * BLK) __attribute__((amdgpu_waves_per_eu(4))) k_mp_dma(const GeomDev<float>* __restrict__ geoms, int ngeom, int gsz,
-                                               int64_t nblocks, const Ctl* __restrict__ ctl) {
+                                               int64_t nblocks, const Ctl* __restrict__ ctl, Red R) {
+    if ((int64_t)blockIdx.x >= nblocks) {
+        series_block<float>(geoms, R, (int)(blockIdx.x - nblocks));
+        return;
+    }
     static_assert(!(LC && FR), "lane compaction needs the haloed region (a wave is not a row)");
     using SH = DmaShape<NH, ZX, FR>;
     constexpr int DTY = SH::DTY, DBLK = SH::DBLK, RREG = SH::RREG, RLD = SH::RLD, STAGE = SH::STAGE;
@@ -924,7 +1039,8 @@ __global__ void __launch_bounds__(NH * BLK) __attribute__((amdgpu_waves_per_eu(4
     const int32_t* const fidx = G.fidx;
     const int s0 = grp * gsz, s1 = min(S, s0 + gsz);
     const int64_t ntile = G.ntile;
-    double* const part = G.part;
+    const int64_t t = ctl->t + R.dt;
+    double* const part = G.part + (t & 1) * G.pstride;
     // the thread's own node
     const int ox = x0 + pos_x(tid), oy = y0 + pos_y(tid), oz = z0 + pos_z(tid);
     const bool oin = ox < nx && oy < ny && oz < nz;
@@ -1015,7 +1131,6 @@ __global__ void __launch_bounds__(NH * BLK) __attribute__((amdgpu_waves_per_eu(4
     double avd[3];
 #pragma unroll
     for (int g = 0; g < 3; ++g) avd[g] = act ? (double)av[g] : 0.0;
-    const int64_t t = ctl->t;
     const uint32_t rbase = hash32((uint32_t)n * 0x9e3779b9u ^ hash32((uint32_t)t ^ ((uint32_t)gi << 24)));
     const float* const Xin = (t & 1) ? G.X1 : G.X0;
     float* const Xout = (t & 1) ? G.X0 : G.X1;
@@ -1301,7 +1416,11 @@ constexpr int GTX = 32, GTY = 4, GTZ = 4;        // ordering tiles (compact stor
 
 template <int NH>
 __global__ void __launch_bounds__(NH * BLK) __attribute__((amdgpu_waves_per_eu(4))) k_mp_gather(
-    const GeomDev<float>* __restrict__ geoms, int ngeom, int gsz, int64_t nblocks, const Ctl* __restrict__ ctl) {
+    const GeomDev<float>* __restrict__ geoms, int ngeom, int gsz, int64_t nblocks, const Ctl* __restrict__ ctl, Red R) {
+    if ((int64_t)blockIdx.x >= nblocks) {
+        series_block<float>(geoms, R, (int)(blockIdx.x - nblocks));
+        return;
+    }
     using GS = GatherShape<NH>;
     constexpr int DBLK = GS::DBLK, NCP = 1, REGION = GS::REG, STAGE = GS::REG + DBLK;
     constexpr int GZSLOT = GS::ZSLOT;
@@ -1330,7 +1449,8 @@ __global__ void __launch_bounds__(NH * BLK) __attribute__((amdgpu_waves_per_eu(4
     const int NC = (int)G.NC;
     const int s0 = grp * gsz, s1 = min(S, s0 + gsz);
     const int64_t ntile = G.ntile;
-    double* const part = G.part;
+    const int64_t t = ctl->t + R.dt;
+    double* const part = G.part + (t & 1) * G.pstride;
     const bool act = tid < C;
     const bool idle = __builtin_amdgcn_readfirstlane(wv * 64 >= C ? 1 : 0) != 0;
     const int i = cbase + (act ? tid : 0);        // compact index of the node
@@ -1361,7 +1481,6 @@ __global__ void __launch_bounds__(NH * BLK) __attribute__((amdgpu_waves_per_eu(4
     double avd[3];
 #pragma unroll
     for (int g = 0; g < 3; ++g) avd[g] = act ? (double)av[g] : 0.0;
-    const int64_t t = ctl->t;
     const uint32_t rbase = hash32((uint32_t)n * 0x9e3779b9u ^ hash32((uint32_t)t ^ ((uint32_t)gi << 24)));
     const float* const Xin = (t & 1) ? G.X1 : G.X0;
     float* const Xout = (t & 1) ? G.X0 : G.X1;
@@ -1570,7 +1689,11 @@ __device__ __forceinline__ int sum_slot(int q, int j) { return j == 0 ? (q == 0 
 // with this.
 template <typename T, int QB>
 __global__ void __launch_bounds__(BLK) k_mp_flat(const GeomDev<T>* __restrict__ geoms, int ngeom, int nqb,
-                                                 int64_t nblocks, const Ctl* __restrict__ ctl) {
+                                                 int64_t nblocks, const Ctl* __restrict__ ctl, Red R) {
+    if ((int64_t)blockIdx.x >= nblocks) {
+        series_block<T>(geoms, R, (int)(blockIdx.x - nblocks));
+        return;
+    }
     __shared__ double wsum[BLK / 64][2 * QB];
     constexpr int E = (int)sizeof(T);
     T* const tag = nullptr;
@@ -1587,7 +1710,8 @@ __global__ void __launch_bounds__(BLK) k_mp_flat(const GeomDev<T>* __restrict__ 
     const bool in = n < (uint32_t)N;
     const bool act = in && G.cls[in ? n : 0] != 0;
     const int64_t ntile = G.ntile;
-    double* const part = G.part + ((int64_t)s * ntile + tile) * NRED;
+    const int64_t t = ctl->t + R.dt;
+    double* const part = G.part + (t & 1) * G.pstride + ((int64_t)s * ntile + tile) * NRED;
     const bool only_q0 = QB == 1 && nqb == 1;
     if (!__syncthreads_or(act)) {  // no fluid node: zero sums
         if (threadIdx.x < 2 * QB) part[sum_slot(q0 + threadIdx.x / 2, threadIdx.x & 1)] = 0.0;
@@ -1603,7 +1727,6 @@ __global__ void __launch_bounds__(BLK) k_mp_flat(const GeomDev<T>* __restrict__ 
 #pragma unroll
     for (int k = 0; k < NL; ++k)
         off[k] = act ? (int)(zo[1 - lcz(k)] + yo[1 - lcy(k)] + xo[1 - lcx(k)]) * E : OOB;
-    const int64_t t = ctl->t;
     const T* const Xin = (t & 1) ? G.X1 : G.X0;
     T* const Xout = (t & 1) ? G.X0 : G.X1;
     const int sl = act ? G.slot[n] : -1;
@@ -1808,113 +1931,6 @@ __global__ void __launch_bounds__(BS) k_mp_resident(const GeomDev<T>* __restrict
         }
     }
 }
-
-// Lattices with many tiles: chunks of RCH tile partials of every
-// (geometry, species) summed by one block each, in a fixed order, into
-// chunk[work][chunk][NRED]; k_mp_reduce then adds the chunks.
-constexpr int RCH = 2048;
-
-template <typename T>
-__global__ void __launch_bounds__(BLK) k_mp_reduce_chunks(const GeomDev<T>* __restrict__ geoms,
-                                                          const int32_t* __restrict__ work, int nch,
-                                                          double* __restrict__ chunk) {
-    __shared__ double lds[NRED * BLK];
-    const int w = blockIdx.x / nch, c = blockIdx.x % nch;
-    const int gi = work[2 * w], s = work[2 * w + 1];
-    const GeomDev<T>& G = geoms[gi];
-    const int64_t ntile = G.ntile;
-    using gdp = const __attribute__((address_space(1))) double*;  // global loads, not flat
-    const gdp P = (gdp)(G.part + (int64_t)s * ntile * NRED);
-    const int64_t i0 = (int64_t)c * RCH, i1 = min(ntile, i0 + RCH);
-    double acc[NRED];
-#pragma unroll
-    for (int k = 0; k < NRED; ++k) acc[k] = 0.0;
-    for (int64_t i = i0 + threadIdx.x; i < i1; i += BLK)
-#pragma unroll
-        for (int k = 0; k < NRED; ++k) acc[k] += P[i * NRED + k];
-    double r;
-    block_sum8(acc, lds, r);
-    if (threadIdx.x < NRED) chunk[((int64_t)w * nch + c) * NRED + threadIdx.x] = r;
-}
-
-// Sum the block partials (or, with nch > 0, the chunk sums) of every
-// (geometry, species) into the series at the current time, in a fixed order,
-// one block of RED_T threads per pair, then advance the time: the partials of
-// a pair are read as one flat array (thread i adds entries i, i + RED_T, ...,
-// all of sum i % NRED, in turn into eight accumulators), the 32 threads of
-// each sum are added by a fixed tree, and the last block to finish moves the
-// state time on (every block has read it by then).
-constexpr int RED_T = 256;
-
-template <typename T>
-__global__ void __launch_bounds__(RED_T) k_mp_reduce(const GeomDev<T>* __restrict__ geoms, int ngeom,
-                                                     const int32_t* __restrict__ work, int nwork, int nch,
-                                                     const double* __restrict__ chunk, Ctl* __restrict__ ctl) {
-    static_assert(RED_T % (64 * 1) == 0 && 64 % NRED == 0, "a thread's entries belong to one sum");
-    __shared__ double wsum[RED_T / 64][NRED];
-    __shared__ bool last;
-    const int w = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int64_t t = ctl->t;
-    const int gi = work[2 * w], s = work[2 * w + 1];
-    const GeomDev<T>& G = geoms[gi];
-    const int64_t ntile = nch > 0 ? nch : G.ntile;
-    // global address space: flat loads would also count as LDS traffic and
-    // serialise the loads below
-    using gdp = const __attribute__((address_space(1))) double*;
-    const gdp P = (gdp)(nch > 0 ? chunk + (int64_t)w * nch * NRED : G.part + (int64_t)s * G.ntile * NRED);
-    const int64_t len = ntile * NRED;
-    // eight loads in flight per thread, then their sums (eight accumulators)
-    double acc[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) acc[u] = 0.0;
-    int64_t i = tid;
-    for (; i + 7 * RED_T < len; i += 8 * RED_T) {
-        double x[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) x[u] = P[i + u * RED_T];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) acc[u] += x[u];
-    }
-#pragma unroll
-    for (int u = 0; u < 7; ++u)
-        if (i + u * RED_T < len) acc[u] += P[i + u * RED_T];
-    double v = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
-    // lanes l, l ^ 8, l ^ 16, ... hold the same sum (l % 8)
-    v += __shfl_xor(v, 8, 64);
-    v += __shfl_xor(v, 16, 64);
-    v += __shfl_xor(v, 32, 64);
-    if (lane < NRED) wsum[wv][lane] = v;
-    __syncthreads();
-    if (tid < NRED && t <= ctl->tmax) {
-        double r = wsum[0][tid];
-#pragma unroll
-        for (int k = 1; k < RED_T / 64; ++k) r += wsum[k][tid];
-        G.series[((t - 1) * G.S + s) * NRED + tid] = r;
-    }
-    if (tid == 0 && t <= ctl->tmax) {
-        // total probability of the species (slots 3 and 7, summed as above)
-        double m = wsum[0][3], a = wsum[0][7];
-#pragma unroll
-        for (int k = 1; k < RED_T / 64; ++k) {
-            m += wsum[k][3];
-            a += wsum[k][7];
-        }
-        if (!(fabs(m + a - ctl->mass_ref) <= ctl->drift_max))
-            atomicMin(reinterpret_cast<unsigned long long*>(&ctl->bad_t), (unsigned long long)t);
-    }
-    // time advance by the last block
-    __syncthreads();
-    if (tid == 0) {
-        __threadfence();
-        last = atomicAdd(&ctl->done, 1u) == (unsigned)(gridDim.x - 1);
-    }
-    __syncthreads();
-    if (last && tid == 0) {
-        ctl->done = 0;
-        ctl->t = t + 1;
-    }
-}
-
 
 // ------------------------------------------------------------------ set-up
 // Link probabilities of Eq. 8 (local equilibrium), FP64, per node and link;
@@ -2276,7 +2292,7 @@ struct lbmp_mp {
     lbmp::Ctl* ctl;
     int32_t* work;
     int nwork;
-    double* chunk;   // [nwork][nch_max][NRED] chunk sums of the series reduction
+    double* chunk;   // [2][nwork][nch_max][NRED] chunk sums of the series reduction
     int nch_max, nch;
     double* setup_tmp;
     // variant 0: direct loads, 1: LDS-staged box, 2: z-march, 3-7: LDS DMA, 8: gathered chunks (FP32),
@@ -2350,7 +2366,7 @@ void carve_geom(GeomHost& g, Carver& c, int64_t tmax) {
     }
     g.coef = c.take<T>(S * 4);
     g.prob = c.take<T>(S * 2);
-    g.part = c.take<double>(S * g.ntile_max * NRED);
+    g.part = c.take<double>(2 * S * g.ntile_max * NRED);
     g.series = c.take<double>((size_t)std::max<int64_t>(tmax, 1) * S * NRED);
     g.spc = c.take<double>(S * 5);
     g.spc0 = c.take<double>(S * 7);
@@ -2377,7 +2393,7 @@ lbmp_status carve_all(lbmp_mp* h, Carver& c) {
     int64_t tmx = 1;
     for (auto& g : h->g) tmx = std::max(tmx, g.ntile_max);
     h->nch_max = (int)((tmx + RCH - 1) / RCH);
-    h->chunk = c.take<double>((size_t)nw * h->nch_max * NRED);
+    h->chunk = c.take<double>(2 * (size_t)nw * h->nch_max * NRED);
     return LBMP_OK;
 }
 
@@ -2458,10 +2474,19 @@ void launch_resident(lbmp_mp* h, int n, hipStream_t s) {
     else k_mp_resident<T, 512, res_npt(8 * sizeof(T))><<<grid, 512, 0, s>>>(G, h->ngeom, nq, n, h->ctl);
 }
 
+// Step `dt` of a call (0 the first), with the blocks that record what the
+// steps before it in the same call have left.
 template <typename T>
-void launch_step_kernel(lbmp_mp* h, hipStream_t s) {
+void launch_step_kernel(lbmp_mp* h, int dt, hipStream_t s) {
     auto* G = static_cast<const GeomDev<T>*>(h->geoms_dev);
-    dim3 grid((unsigned)h->nblocks);
+    Red R{h->work, h->chunk, h->ctl, h->nwork, h->nch, 0, 0, dt};
+    if (h->nch > 1) {
+        R.n1 = dt >= 1 ? h->nwork * h->nch : 0;
+        R.n2 = dt >= 2 ? h->nwork : 0;
+    } else {
+        R.n2 = dt >= 1 ? h->nwork : 0;
+    }
+    dim3 grid((unsigned)(h->nblocks + R.n1 + R.n2));
     if (h->variant == 10) {
         launch_resident<T>(h, 1, s);
         return;
@@ -2469,72 +2494,75 @@ void launch_step_kernel(lbmp_mp* h, hipStream_t s) {
     if (h->variant == 9) {
         const int nqb = nquant(h) / h->K;
         switch (h->K) {
-            case 1: k_mp_flat<T, 1><<<grid, BLK, 0, s>>>(G, h->ngeom, nqb, h->nblocks, h->ctl); break;
-            case 2: k_mp_flat<T, 2><<<grid, BLK, 0, s>>>(G, h->ngeom, nqb, h->nblocks, h->ctl); break;
-            default: k_mp_flat<T, 4><<<grid, BLK, 0, s>>>(G, h->ngeom, nqb, h->nblocks, h->ctl); break;
+            case 1: k_mp_flat<T, 1><<<grid, BLK, 0, s>>>(G, h->ngeom, nqb, h->nblocks, h->ctl, R); break;
+            case 2: k_mp_flat<T, 2><<<grid, BLK, 0, s>>>(G, h->ngeom, nqb, h->nblocks, h->ctl, R); break;
+            default: k_mp_flat<T, 4><<<grid, BLK, 0, s>>>(G, h->ngeom, nqb, h->nblocks, h->ctl, R); break;
         }
         return;
     }
     if (h->variant >= 3) {
         if constexpr (std::is_same<T, float>::value) {
-            if (h->variant == 4) k_mp_dma<2, true, false><<<grid, 2 * BLK, 0, s>>>(G, h->ngeom, h->gsz, h->nblocks, h->ctl);
-            else if (h->variant == 5) k_mp_dma<2, false, true><<<grid, 2 * BLK, 0, s>>>(G, h->ngeom, h->gsz, h->nblocks, h->ctl);
-            else if (h->variant == 6 && h->K == 4) k_mp_dma<4, true, true><<<grid, 4 * BLK, 0, s>>>(G, h->ngeom, h->gsz, h->nblocks, h->ctl);
-            else if (h->variant == 6) k_mp_dma<2, true, true><<<grid, 2 * BLK, 0, s>>>(G, h->ngeom, h->gsz, h->nblocks, h->ctl);
-            else if (h->variant == 7) k_mp_dma<2, true, false, true><<<grid, 2 * BLK, 0, s>>>(G, h->ngeom, h->gsz, h->nblocks, h->ctl);
-            else if (h->variant == 8 && h->g[0].gnh == 1) k_mp_gather<1><<<grid, BLK, 0, s>>>(G, h->ngeom, h->gsz, h->nblocks, h->ctl);
-            else if (h->variant == 8) k_mp_gather<2><<<grid, 2 * BLK, 0, s>>>(G, h->ngeom, h->gsz, h->nblocks, h->ctl);
-            else if (h->K == 2) k_mp_dma<2, false, false><<<grid, 2 * BLK, 0, s>>>(G, h->ngeom, h->gsz, h->nblocks, h->ctl);
-            else k_mp_dma<1, false, false><<<grid, BLK, 0, s>>>(G, h->ngeom, h->gsz, h->nblocks, h->ctl);
+            if (h->variant == 4) k_mp_dma<2, true, false><<<grid, 2 * BLK, 0, s>>>(G, h->ngeom, h->gsz, h->nblocks, h->ctl, R);
+            else if (h->variant == 5) k_mp_dma<2, false, true><<<grid, 2 * BLK, 0, s>>>(G, h->ngeom, h->gsz, h->nblocks, h->ctl, R);
+            else if (h->variant == 6 && h->K == 4) k_mp_dma<4, true, true><<<grid, 4 * BLK, 0, s>>>(G, h->ngeom, h->gsz, h->nblocks, h->ctl, R);
+            else if (h->variant == 6) k_mp_dma<2, true, true><<<grid, 2 * BLK, 0, s>>>(G, h->ngeom, h->gsz, h->nblocks, h->ctl, R);
+            else if (h->variant == 7) k_mp_dma<2, true, false, true><<<grid, 2 * BLK, 0, s>>>(G, h->ngeom, h->gsz, h->nblocks, h->ctl, R);
+            else if (h->variant == 8 && h->g[0].gnh == 1) k_mp_gather<1><<<grid, BLK, 0, s>>>(G, h->ngeom, h->gsz, h->nblocks, h->ctl, R);
+            else if (h->variant == 8) k_mp_gather<2><<<grid, 2 * BLK, 0, s>>>(G, h->ngeom, h->gsz, h->nblocks, h->ctl, R);
+            else if (h->K == 2) k_mp_dma<2, false, false><<<grid, 2 * BLK, 0, s>>>(G, h->ngeom, h->gsz, h->nblocks, h->ctl, R);
+            else k_mp_dma<1, false, false><<<grid, BLK, 0, s>>>(G, h->ngeom, h->gsz, h->nblocks, h->ctl, R);
         }
         return;
     }
     if (h->variant == 2) {
         switch (h->gsz) {
-            case 1: k_mp_march<T, 1><<<grid, BLK, 0, s>>>(G, h->ngeom, h->nblocks, h->K, h->ctl); break;
-            case 2: k_mp_march<T, 2><<<grid, BLK, 0, s>>>(G, h->ngeom, h->nblocks, h->K, h->ctl); break;
-            default: k_mp_march<T, 4><<<grid, BLK, 0, s>>>(G, h->ngeom, h->nblocks, h->K, h->ctl); break;
+            case 1: k_mp_march<T, 1><<<grid, BLK, 0, s>>>(G, h->ngeom, h->nblocks, h->K, h->ctl, R); break;
+            case 2: k_mp_march<T, 2><<<grid, BLK, 0, s>>>(G, h->ngeom, h->nblocks, h->K, h->ctl, R); break;
+            default: k_mp_march<T, 4><<<grid, BLK, 0, s>>>(G, h->ngeom, h->nblocks, h->K, h->ctl, R); break;
         }
         return;
     }
     if (h->variant == 1) {
-        if (h->K == 1) k_mp_step_box<T, 1><<<grid, BLK, 0, s>>>(G, h->ngeom, h->gsz, h->nblocks, h->ctl);
-        else k_mp_step_box<T, 2><<<grid, BLK, 0, s>>>(G, h->ngeom, h->gsz, h->nblocks, h->ctl);
+        if (h->K == 1) k_mp_step_box<T, 1><<<grid, BLK, 0, s>>>(G, h->ngeom, h->gsz, h->nblocks, h->ctl, R);
+        else k_mp_step_box<T, 2><<<grid, BLK, 0, s>>>(G, h->ngeom, h->gsz, h->nblocks, h->ctl, R);
         return;
     }
     switch (h->K) {
-        case 1: k_mp_step<T, 1><<<grid, BLK, 0, s>>>(G, h->ngeom, h->gsz, h->nblocks, h->ctl); break;
-        default: k_mp_step<T, 2><<<grid, BLK, 0, s>>>(G, h->ngeom, h->gsz, h->nblocks, h->ctl); break;
+        case 1: k_mp_step<T, 1><<<grid, BLK, 0, s>>>(G, h->ngeom, h->gsz, h->nblocks, h->ctl, R); break;
+        default: k_mp_step<T, 2><<<grid, BLK, 0, s>>>(G, h->ngeom, h->gsz, h->nblocks, h->ctl, R); break;
     }
 }
 
+// After n steps: the rest of their sums, and the state time.
 template <typename T>
-void launch_step_tail(lbmp_mp* h, hipStream_t s) {
-    if (h->variant == 10) return;  // the kernel records its sums and moves the time itself
+void launch_tail(lbmp_mp* h, int n, hipStream_t s) {
     auto* G = static_cast<const GeomDev<T>*>(h->geoms_dev);
-    if (h->nch > 1)
-        k_mp_reduce_chunks<T><<<(unsigned)(h->nwork * h->nch), BLK, 0, s>>>(G, h->work, h->nch, h->chunk);
-    k_mp_reduce<T><<<(unsigned)h->nwork, RED_T, 0, s>>>(G, h->ngeom, h->work, h->nwork, h->nch > 1 ? h->nch : 0,
-                                                         h->chunk, h->ctl);
+    Red R{h->work, h->chunk, h->ctl, h->nwork, h->nch, 0, h->nwork, n};
+    if (h->nch > 1) {
+        R.n1 = h->nwork * h->nch;
+        R.n2 = n >= 2 ? h->nwork : 0;
+        k_mp_tail<T><<<(unsigned)(R.n1 + R.n2), BLK, 0, s>>>(G, R, 0);
+        R.n1 = 0;
+        R.n2 = h->nwork;
+        R.dt = n + 1;
+    }
+    k_mp_tail<T><<<(unsigned)R.n2, BLK, 0, s>>>(G, R, n);
 }
 
 template <typename T>
-void launch_step(lbmp_mp* h, hipStream_t s) {
-    launch_step_kernel<T>(h, s);
-    launch_step_tail<T>(h, s);
-}
-
-void do_steps(lbmp_mp* h, int64_t n, hipStream_t s) {
-    if (h->variant == 10) {
-        for (; n > 0; n -= RES_CHUNK) {
-            const int m = (int)std::min<int64_t>(n, RES_CHUNK);
-            if (h->prec == LBMP_FP32) launch_resident<float>(h, m, s); else launch_resident<double>(h, m, s);
-        }
+void do_steps_t(lbmp_mp* h, int64_t n, hipStream_t s) {
+    if (n <= 0) return;
+    if (h->variant == 10) {  // the kernel records its sums and moves the time itself
+        for (; n > 0; n -= RES_CHUNK) launch_resident<T>(h, (int)std::min<int64_t>(n, RES_CHUNK), s);
         return;
     }
-    for (int64_t i = 0; i < n; ++i) {
-        if (h->prec == LBMP_FP32) launch_step<float>(h, s); else launch_step<double>(h, s);
-    }
+    for (int i = 0; i < (int)n; ++i) launch_step_kernel<T>(h, i, s);
+    launch_tail<T>(h, (int)n, s);
+}
+
+// n steps (at most a few hundred unless resident: n counts launches)
+void do_steps(lbmp_mp* h, int64_t n, hipStream_t s) {
+    if (h->prec == LBMP_FP32) do_steps_t<float>(h, n, s); else do_steps_t<double>(h, n, s);
 }
 
 // The haloed LDS-DMA blocks store the fields of fluid nodes only (a porous
@@ -2578,6 +2606,7 @@ lbmp_status upload_geoms(lbmp_mp* h) {
         d.coef = (const T*)g.coef; d.prob = (const T*)g.prob;
         d.kc = g.kc;
         d.part = g.part; d.series = g.series;
+        d.pstride = (int64_t)g.S * d.ntile * NRED;
     }
     h->nblocks = blk;
     int64_t tmx = 1;
@@ -3620,9 +3649,11 @@ extern "C" lbmp_status mp_profile_steps(lbmp_mp* h, int64_t n_steps, double* ms_
     LBMP_HIP(hipEventRecord(ev[2 * n_steps], s));
     for (int64_t i = 0; i < n_steps; ++i) {
         LBMP_HIP(hipEventRecord(ev[2 * i], s));
-        if (h->prec == LBMP_FP32) launch_step_kernel<float>(h, s); else launch_step_kernel<double>(h, s);
+        if (h->prec == LBMP_FP32) launch_step_kernel<float>(h, 0, s); else launch_step_kernel<double>(h, 0, s);
         LBMP_HIP(hipEventRecord(ev[2 * i + 1], s));
-        if (h->prec == LBMP_FP32) launch_step_tail<float>(h, s); else launch_step_tail<double>(h, s);
+        if (h->variant != 10) {
+            if (h->prec == LBMP_FP32) launch_tail<float>(h, 1, s); else launch_tail<double>(h, 1, s);
+        }
     }
     LBMP_HIP(hipEventRecord(ev[2 * n_steps + 1], s));
     LBMP_HIP(hipEventSynchronize(ev[2 * n_steps + 1]));
