@@ -1706,50 +1706,49 @@ __global__ void __launch_bounds__(BLK) k_mp_flat(const GeomDev<T>* __restrict__ 
     const int s = (int)(sq / nqb), q0 = (int)(sq % nqb) * QB;
     const uint32_t nx = G.nx, ny = G.ny, nz = G.nz, plane = nx * ny;
     const int N = (int)G.N;
+    // Every load but the adsorbed values goes out before the first is waited
+    // for: a solid node's fields and table entries are zeros, so its class
+    // masks the stores only.
     const uint32_t n = tile * BLK + threadIdx.x;
     const bool in = n < (uint32_t)N;
-    const bool act = in && G.cls[in ? n : 0] != 0;
     const int64_t ntile = G.ntile;
     const int64_t t = ctl->t + R.dt;
     double* const part = G.part + (t & 1) * G.pstride + ((int64_t)s * ntile + tile) * NRED;
     const bool only_q0 = QB == 1 && nqb == 1;
-    if (!__syncthreads_or(act)) {  // no fluid node: zero sums
-        if (threadIdx.x < 2 * QB) part[sum_slot(q0 + threadIdx.x / 2, threadIdx.x & 1)] = 0.0;
-        if (only_q0 && threadIdx.x < NRED) part[threadIdx.x] = 0.0;
-        return;
-    }
-    const uint32_t m = act ? n : 0, z = m / plane, r2 = m - z * plane, y = r2 / nx, x = r2 - y * nx;
+    const uint32_t m = in ? n : 0, z = m / plane, r2 = m - z * plane, y = r2 / nx, x = r2 - y * nx;
+    const int cls = G.cls[m];
+    const int32_t slot = G.slot[m];
     const uint32_t xo[3] = {x == 0 ? nx - 1 : x - 1, x, x + 1 == nx ? 0 : x + 1};
     const uint32_t yo[3] = {(y == 0 ? ny - 1 : y - 1) * nx, y * nx, (y + 1 == ny ? 0 : y + 1) * nx};
     const uint32_t zo[3] = {(z == 0 ? nz - 1 : z - 1) * plane, z * plane, (z + 1 == nz ? 0 : z + 1) * plane};
-    const int offn = act ? (int)n * E : OOB;
+    const int offm = in ? (int)n * E : OOB;
     int off[NL];  // source r - c_k of link k
 #pragma unroll
     for (int k = 0; k < NL; ++k)
-        off[k] = act ? (int)(zo[1 - lcz(k)] + yo[1 - lcy(k)] + xo[1 - lcx(k)]) * E : OOB;
+        off[k] = in ? (int)(zo[1 - lcz(k)] + yo[1 - lcy(k)] + xo[1 - lcx(k)]) * E : OOB;
     const T* const Xin = (t & 1) ? G.X1 : G.X0;
     T* const Xout = (t & 1) ? G.X0 : G.X1;
-    const int sl = act ? G.slot[n] : -1;
-    const bool isI = sl >= 0;
-    const int offa = isI ? sl * E : OOB;
     const int64_t NI = G.NI;
     T v[QB][NL], xc[QB], xa[QB], pin[NL], av[QB];
 #pragma unroll
     for (int j = 0; j < QB; ++j) {
         const int64_t f = 4 * s + q0 + j;
         const auto rin = mkrsrc(Xin + f * N, (int64_t)N * E);
-        xc[j] = bload(tag, rin, offn);
+        xc[j] = bload(tag, rin, offm);
 #pragma unroll
         for (int k = 0; k < NL; ++k) v[j][k] = bload(tag, rin, off[k]);
-        xa[j] = bload(tag, mkrsrc(G.Xa + f * NI, NI * E), offa);
     }
 #pragma unroll
-    for (int k = 0; k < NL; ++k) pin[k] = bload(tag, mkrsrc(G.pin + (int64_t)k * N, (int64_t)N * E), offn);
-    const double sig = bload(dtag, mkrsrc(G.sig, (int64_t)N * 8), act ? (int)n * 8 : OOB);
-    const double src = (double)bload(tag, mkrsrc(G.src, (int64_t)N * E), offn);
+    for (int k = 0; k < NL; ++k) pin[k] = bload(tag, mkrsrc(G.pin + (int64_t)k * N, (int64_t)N * E), offm);
+    const double sig = bload(dtag, mkrsrc(G.sig, (int64_t)N * 8), in ? (int)n * 8 : OOB);
+    const double src = (double)bload(tag, mkrsrc(G.src, (int64_t)N * E), offm);
 #pragma unroll
     for (int j = 0; j < QB; ++j)
-        av[j] = q0 + j > 0 ? bload(tag, mkrsrc(G.a + (int64_t)(q0 + j - 1) * N, (int64_t)N * E), offn) : T(0);
+        av[j] = q0 + j > 0 ? bload(tag, mkrsrc(G.a + (int64_t)(q0 + j - 1) * N, (int64_t)N * E), offm) : T(0);
+    const bool act = in && cls != 0, isI = act && slot >= 0;
+    const int offn = act ? (int)n * E : OOB, offa = isI ? slot * E : OOB;
+#pragma unroll
+    for (int j = 0; j < QB; ++j) xa[j] = bload(tag, mkrsrc(G.Xa + (int64_t)(4 * s + q0 + j) * NI, NI * E), offa);
     const double pa = (double)G.prob[2 * s], pd = (double)G.prob[2 * s + 1];
     const uint32_t rbase = hash32((act ? n : 0u) * 0x9e3779b9u ^ hash32((uint32_t)t ^ ((uint32_t)gi << 24)));
     uint32_t rs = hash32(rbase ^ ((uint32_t)s * 0x632be5abu)) | 1u;
