@@ -40,6 +40,7 @@ __host__ __device__ constexpr int woff(int l) {
 }
 __host__ __device__ constexpr int boff(int l) { return woff(l) + tout(l) * tin(l); }
 constexpr int NPAR = woff(NLAYER);
+constexpr int SQ = WIDTH * WIDTH;
 static_assert(boff(0) % 4 == 0 && boff(1) % 4 == 0 && boff(2) % 4 == 0, "hidden biases are read four at a time");
 static_assert(boff(2) - boff(1) == boff(1) - boff(0), "hidden biases at one stride");
 
@@ -60,87 +61,140 @@ __host__ __device__ constexpr int frag(int row, int k, int ks) {
 __device__ __forceinline__ float sigm(float z) { return __builtin_amdgcn_rcpf(1.0f + __expf(-z)); }
 __device__ __forceinline__ float silu(float z) { return z * sigm(z); }
 
-// Fused inference: one block (8 waves) per FS samples runs all four layers
-// with the activations in LDS (one buffer: a layer's products read it, and
-// after a barrier its epilogue overwrites it) and the weights read as MFMA
-// operands straight from global memory, where all blocks share them in L2;
-// each weight fragment a wave loads serves the block's 128 samples. The
-// arithmetic is that of the training pass (bf16 operands, fp32 accumulation in
-// increasing K, bias and SiLU in fp32, activations rounded to bf16).
-constexpr int FS = 128;              // samples per block
-constexpr int FWAVES = 8;            // waves per block
 constexpr int APITCH = WIDTH + 8;    // bf16 per activation row (padded against bank conflicts)
+constexpr int XPITCH = PAD_IN + 8;
+constexpr int FBLOCKS = 256;         // one per CU
 
-__global__ void __launch_bounds__(64 * FWAVES) __attribute__((amdgpu_waves_per_eu(4)))
-k_mlp_forward(const float* __restrict__ x, int64_t n, const float* __restrict__ norm,
-              const __bf16* __restrict__ W0, const float* __restrict__ b0, const __bf16* __restrict__ W1,
-              const float* __restrict__ b1, const __bf16* __restrict__ W2, const float* __restrict__ b2,
-              const __bf16* __restrict__ W3, const float* __restrict__ b3, float* __restrict__ y) {
-    __shared__ __align__(16) __bf16 act[FS * APITCH];
-    const int64_t s0 = (int64_t)blockIdx.x * FS;
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int r = lane & 31, kh = (lane >> 5) * 8;
-    // normalised features, zero padded to PAD_IN columns
-    for (int i = t; i < FS * PAD_IN; i += 64 * FWAVES) {
-        const int row = i / PAD_IN, c = i % PAD_IN;
-        const int64_t si = s0 + row;
-        float v = 0.0f;
-        if (c < NFEAT && si < n) v = (x[si * NFEAT + c] - norm[c]) / norm[6 + c];
-        act[row * APITCH + c] = (__bf16)v;
-    }
-    __syncthreads();
-    // hidden layer: wave w computes output features 32 w .. 32 w + 31 of all
-    // FS samples as the transposed product (weights as the MFMA's first
-    // operand), so each lane holds runs of 4 consecutive features of one
-    // sample and writes them to LDS as one 8-byte store
-    constexpr int ST = FS / 32;  // sample tiles
-    auto hidden = [&](const __bf16* __restrict__ W, const float* __restrict__ bias, int K) {
-        const int n0 = 32 * wave;
-        f32x16 acc[ST] = {};
-#pragma unroll 2
-        for (int k0 = 0; k0 < K; k0 += 16) {
-            const bf16x8 w = *reinterpret_cast<const bf16x8*>(W + frag(n0, k0, K / 16) + lane * 8);
-            bf16x8 a[ST];
+// Barrier for data passed through LDS: waits for this wave's LDS operations
+// only. __syncthreads() also waits for every global store and load in flight,
+// which nothing in the block depends on.
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0), vmcnt and expcnt at their maxima
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// Fused inference. A block of 8 waves takes groups of 32 ST samples through
+// all four layers, wave w computing features 32 w .. 32 w + 31 of every layer
+// as the transposed product (weights first), so each lane holds runs of 4
+// consecutive features of one sample and writes them to LDS as one 8-byte
+// store. The weights of the three hidden layers stay in the wave's registers
+// for all groups (136 VGPRs); activations alternate between two LDS buffers,
+// one barrier per layer; the output layer runs on ST waves, by turns, while the
+// others start the next group. Within a layer the products of one 32-sample
+// tile are issued between the activations of the tile before, so that MFMA and
+// VALU overlap inside a wave. Bound by the SiLU: 768 per sample, an
+// exponential, a reciprocal and 5 more VALU operations each.
+// 2^20 rows: 421 us with weights read from the L2 for every group and the
+// epilogue after the products, @@ us now.
+// The arithmetic is that of the training pass (bf16 operands, fp32
+// accumulation in increasing K, bias and SiLU in fp32, activations rounded to
+// bf16).
+template <int ST>
+__global__ void __launch_bounds__(512) k_mlp_forward(const float* __restrict__ x, int64_t n,
+                                                     const float* __restrict__ norm, const __bf16* __restrict__ W0,
+                                                     const __bf16* __restrict__ Wsq, const __bf16* __restrict__ W3,
+                                                     const float* __restrict__ P, float* __restrict__ y) {
+    constexpr int RS = 32 * ST, KS = WIDTH / 16, NX = (RS * NFEAT + 511) / 512;
+    __shared__ __align__(16) __bf16 act[2][RS * APITCH];
+    __shared__ __align__(16) __bf16 xs[RS * XPITCH];
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int r = lane & 31, hi = lane >> 5, kh = hi * 8, n0 = 32 * wave;
+    bf16x8 w0[2], w1[KS], w2[KS];
 #pragma unroll
-            for (int j = 0; j < ST; ++j) a[j] = *reinterpret_cast<const bf16x8*>(act + (32 * j + r) * APITCH + k0 + kh);
+    for (int k = 0; k < 2; ++k) w0[k] = *reinterpret_cast<const bf16x8*>(W0 + frag(n0, 16 * k, 2) + lane * 8);
 #pragma unroll
-            for (int j = 0; j < ST; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, a[j], acc[j], 0, 0, 0);
+    for (int k = 0; k < KS; ++k) w1[k] = *reinterpret_cast<const bf16x8*>(Wsq + frag(n0, 16 * k, KS) + lane * 8);
+#pragma unroll
+    for (int k = 0; k < KS; ++k) w2[k] = *reinterpret_cast<const bf16x8*>(Wsq + SQ + frag(n0, 16 * k, KS) + lane * 8);
+    // normalised features of the group that starts at sample s0, through
+    // registers so that their loads run ahead of the group
+    const int64_t groups = (n + RS - 1) / RS;
+    float xv[NX];
+    auto fetch = [&](int64_t s0) {
+#pragma unroll
+        for (int i = 0; i < NX; ++i) {
+            const int e = t + 512 * i;
+            const int64_t at = s0 * NFEAT + e;
+            xv[i] = e < RS * NFEAT && at < n * NFEAT ? x[at] : 0.0f;
         }
-        __syncthreads();  // every wave has read the layer's input
+    };
+    auto stage = [&](int64_t s0) {
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const int nf = n0 + 8 * g + 4 * (lane >> 5);  // features nf .. nf + 3
-            const float4 bc = *reinterpret_cast<const float4*>(bias + nf);
-#pragma unroll
-            for (int j = 0; j < ST; ++j) {
-                bf16x4 o;
-                o[0] = (__bf16)silu(acc[j][4 * g + 0] + bc.x);
-                o[1] = (__bf16)silu(acc[j][4 * g + 1] + bc.y);
-                o[2] = (__bf16)silu(acc[j][4 * g + 2] + bc.z);
-                o[3] = (__bf16)silu(acc[j][4 * g + 3] + bc.w);
-                *reinterpret_cast<bf16x4*>(act + (32 * j + r) * APITCH + nf) = o;
+        for (int i = 0; i < NX; ++i) {
+            const int e = t + 512 * i;
+            if (e < RS * NFEAT) {
+                const int row = e / NFEAT, c = e % NFEAT;
+                xs[row * XPITCH + c] = s0 + row < n ? (__bf16)((xv[i] - norm[c]) / norm[6 + c]) : (__bf16)0.0f;
             }
         }
     };
-    hidden(W0, b0, PAD_IN);
-    __syncthreads();
-    hidden(W1, b1, WIDTH);
-    __syncthreads();
-    hidden(W2, b2, WIDTH);
-    __syncthreads();
-    // output layer (PAD_OUT features, feature 0 is the network's output), also
-    // transposed: waves 0 .. ST - 1 take samples 32 w .. 32 w + 31; feature 0
-    // of sample 32 w + r sits in element 0 of lane r
-    if (wave < ST) {
-        f32x16 acc = {};
-#pragma unroll 4
-        for (int k0 = 0; k0 < WIDTH; k0 += 16) {
-            const bf16x8 w = *reinterpret_cast<const bf16x8*>(W3 + frag(0, k0, WIDTH / 16) + lane * 8);
-            const bf16x8 a = *reinterpret_cast<const bf16x8*>(act + (32 * wave + r) * APITCH + k0 + kh);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, a, acc, 0, 0, 0);
+    for (int i = t; i < RS * (PAD_IN - NFEAT); i += 512)
+        xs[i / (PAD_IN - NFEAT) * XPITCH + NFEAT + i % (PAD_IN - NFEAT)] = (__bf16)0.0f;
+    if ((int64_t)blockIdx.x < groups) {
+        fetch((int64_t)blockIdx.x * RS);
+        stage((int64_t)blockIdx.x * RS);
+    }
+    lds_barrier();
+    // one hidden layer: in (pitch ip) -> out
+    auto hidden = [&](const bf16x8* w, auto ksc, const __bf16* in, int ip, const float* __restrict__ bias, __bf16* out) {
+        constexpr int ks = decltype(ksc)::value;
+        auto product = [&](int j) {
+            f32x16 acc = {};
+#pragma unroll
+            for (int k = 0; k < ks; ++k)
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                    w[k], *reinterpret_cast<const bf16x8*>(in + (32 * j + r) * ip + 16 * k + kh), acc, 0, 0, 0);
+            return acc;
+        };
+        float4 bc[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) bc[g] = *reinterpret_cast<const float4*>(bias + n0 + 8 * g + 4 * hi);
+        f32x16 acc = product(0);
+#pragma unroll
+        for (int j = 0; j < ST; ++j) {
+            f32x16 nxt = {};
+            if (j + 1 < ST) nxt = product(j + 1);
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                bf16x4 o;
+                o[0] = (__bf16)silu(acc[4 * g + 0] + bc[g].x);
+                o[1] = (__bf16)silu(acc[4 * g + 1] + bc[g].y);
+                o[2] = (__bf16)silu(acc[4 * g + 2] + bc[g].z);
+                o[3] = (__bf16)silu(acc[4 * g + 3] + bc[g].w);
+                *reinterpret_cast<bf16x4*>(out + (32 * j + r) * APITCH + n0 + 8 * g + 4 * hi) = o;
+            }
+            acc = nxt;
         }
-        const int64_t si = s0 + 32 * wave + r;
-        if (lane < 32 && si < n) y[si] = norm[12] + norm[13] * (acc[0] + b3[0]);
+    };
+    int turn = 0;
+    for (int64_t grp = blockIdx.x; grp < groups; grp += gridDim.x, turn ^= 1) {
+        const int64_t s0 = grp * RS, s1 = s0 + (int64_t)gridDim.x * RS;
+        // a group's buffers are the last one's, swapped: its output layer may
+        // still be reading act[turn ^ 1] while this one fills act[turn]
+        __bf16 *const A = act[turn], *const B = act[turn ^ 1];
+        fetch(s1);
+        hidden(w0, std::integral_constant<int, 2>(), xs, XPITCH, P + boff(0), A);
+        lds_barrier();
+        stage(s1);
+        hidden(w1, std::integral_constant<int, KS>(), A, APITCH, P + boff(1), B);
+        lds_barrier();
+        hidden(w2, std::integral_constant<int, KS>(), B, APITCH, P + boff(2), A);
+        lds_barrier();
+        // output layer (PAD_OUT features, feature 0 is the network's output), also
+        // transposed: feature 0 of sample 32 j + r sits in element 0 of lane r
+        const int j = (wave + (turn ? ST : 0)) & 7;
+        if (j < ST) {
+            f32x16 acc = {};
+#pragma unroll 4
+            for (int k = 0; k < KS; ++k)
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                    *reinterpret_cast<const bf16x8*>(W3 + frag(0, 16 * k, KS) + lane * 8),
+                    *reinterpret_cast<const bf16x8*>(A + (32 * j + r) * APITCH + 16 * k + kh), acc, 0, 0, 0);
+            const int64_t si = s0 + 32 * j + r;
+            if (lane < 32 && si < n) y[si] = norm[12] + norm[13] * (acc[0] + P[boff(3)]);
+        }
     }
 }
 
@@ -149,8 +203,6 @@ constexpr int GSPLIT_MAX = 32;
 // a split's weight-gradient partials: W_1 [256][32], W_2, W_3 [256][256], W_4 [256]; bias partials
 constexpr int GP1 = WIDTH * PAD_IN, GP2 = GP1 + WIDTH * WIDTH, GP3 = GP2 + WIDTH * WIDTH, GP = GP3 + WIDTH;
 constexpr int GPB = 3 * WIDTH + 1;
-
-constexpr int SQ = WIDTH * WIDTH;
 
 struct TrainBufs {
     const float* norm;      // [6] mean, [6] std, y_mean, y_std
@@ -163,16 +215,6 @@ struct TrainBufs {
     size_t lstride;
     float* sq;              // [B] squared errors
 };
-
-// Barrier for data passed through LDS: waits for this wave's LDS operations
-// only. __syncthreads() also waits for every global store and load in flight,
-// which nothing in the block depends on.
-__device__ __forceinline__ void lds_barrier() {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0), vmcnt and expcnt at their maxima
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
 
 // Forward and backward pass of 32 rows (x[idx], y[idx]; idx null: in order) in
 // one block of 8 waves: wave w owns features 32 w .. 32 w + 31 of every layer,
@@ -737,9 +779,17 @@ extern "C" lbmp_status sg_predict(lbmp_sg* h, const float* x_dev, int64_t n, flo
     if (n < 0 || (n > 0 && (!x_dev || !y_dev))) return fail(LBMP_EINVAL, "bad arguments");
     hipStream_t s = h->stream;
     if (n > 0) {
-        k_mlp_forward<<<(unsigned)((n + FS - 1) / FS), 64 * FWAVES, 0, s>>>(
-            x_dev, n, h->norm, h->K.W0, h->P + boff(0), h->K.Wsq, h->P + boff(1), h->K.Wsq + SQ, h->P + boff(2),
-            h->K.W3, h->P + boff(3), y_dev);
+        // samples per group: 32 until every CU has one (least latency), then 64,
+        // then 128 (fewest barriers per sample), a block per CU and group by group
+        auto go = [&](auto stc) {
+            constexpr int ST = decltype(stc)::value;
+            const int64_t groups = (n + 32 * ST - 1) / (32 * ST);
+            k_mlp_forward<ST><<<(unsigned)std::min<int64_t>(groups, FBLOCKS), 512, 0, s>>>(x_dev, n, h->norm, h->K.W0, h->K.Wsq,
+                                                                                    h->K.W3, h->P, y_dev);
+        };
+        if (n <= 32 * FBLOCKS) go(std::integral_constant<int, 1>());
+        else if (n <= 64 * FBLOCKS) go(std::integral_constant<int, 2>());
+        else go(std::integral_constant<int, 4>());
     }
     LBMP_HIP(hipGetLastError());
     return LBMP_OK;
