@@ -136,22 +136,35 @@ def _torch_cuda():
     return torch
 
 
-def _enter(stream, *tensors):
+def _enter(stream, *tensors, event=None, ask=False):
     """Order work queued on `stream` after the caller's current stream (which
     produced the tensors and the workspaces' previous contents), and tell the
-    caching allocator that `stream` uses the tensors."""
+    caching allocator that `stream` uses the tensors; returns the current
+    stream. `event`: one kept by the handle instead of one created here (53 ->
+    45 us for a small predict, which waits both ways). ask: the current stream
+    is idle as a rule between calls (training and propagation steps, whose
+    results stay in the handle), and then has nothing to wait for: asking an
+    idle stream takes 1 us, the event and the wait 17 (asking a busy one 8). A
+    stream being captured must not be asked."""
     import torch
-    stream.wait_stream(torch.cuda.current_stream())
+    cur = torch.cuda.current_stream()
+    if not ask or torch.cuda.is_current_stream_capturing() or not cur.query():
+        stream.wait_event(cur.record_event(event))
     for t in tensors:
         if t is not None:
             t.record_stream(stream)
+    return cur
 
 
-def _leave(stream):
+def _leave(stream, cur, event=None):
     """Order the caller's current stream after the work just queued on `stream`
     (so results can be used there without an explicit synchronisation)."""
+    cur.wait_event(stream.record_event(event))
+
+
+def _event():
     import torch
-    torch.cuda.current_stream().wait_stream(stream)
+    return torch.cuda.Event()
 
 
 def _ptr(a: np.ndarray):
@@ -296,6 +309,7 @@ class MP:
     def __init__(self, handle, ws, flows, n_species, stream, keep):
         self.handle, self.ws, self.flows, self.n_species, self.stream = handle, ws, flows, n_species, stream
         self._keep = keep
+        self._event = _event()
 
     def step(self, n: int):
         mp_step_n(self, n)
@@ -382,7 +396,7 @@ def mp_uptake(mp: MP, geom: int = 0, t0: int = 0, count: int | None = None) -> d
 def mp_step_n(mp: MP, n: int):
     """Queue n steps on the handle's stream (asynchronous; ordered after the
     caller's current stream)."""
-    _enter(mp.stream)
+    _enter(mp.stream, event=mp._event, ask=True)
     _check(_lib.mp_step_n(mp.handle, int(n)))
 
 
@@ -463,6 +477,7 @@ class Surrogate:
         _check(_lib.sg_workspace_bytes(batch_max, ctypes.byref(nb)))
         self.ws = torch.empty(nb.value, dtype=torch.uint8, device="cuda")
         self.stream = stream or torch.cuda.Stream()
+        self._event, self._done = _event(), _event()
         _enter(self.stream, self.ws)
         self.batch_max = batch_max
         h = ctypes.c_void_p()
@@ -491,7 +506,7 @@ class Surrogate:
     def train_step(self, x, y, idx, B: int, lr: float, want_loss: bool = False):
         """x, y: torch float32 CUDA tensors (n, 6), (n,); idx: int32 CUDA tensor (>= B) or None."""
         loss = ctypes.c_float()
-        _enter(self.stream, x, y, idx)
+        _enter(self.stream, x, y, idx, event=self._event, ask=True)
         _check(_lib.sg_train_step(self.handle, ctypes.c_void_p(x.data_ptr()), ctypes.c_void_p(y.data_ptr()),
                                   ctypes.c_void_p(idx.data_ptr()) if idx is not None else None, int(B),
                                   float(lr), ctypes.byref(loss) if want_loss else None))
@@ -500,7 +515,7 @@ class Surrogate:
     def gradients(self, x, y, B: int):
         g = np.zeros(self.n_params, dtype=np.float32)
         loss = ctypes.c_float()
-        _enter(self.stream, x, y)
+        _enter(self.stream, x, y, event=self._event)
         _check(_lib.sg_gradients(self.handle, ctypes.c_void_p(x.data_ptr()), ctypes.c_void_p(y.data_ptr()),
                                  int(B), _ptr(g), ctypes.byref(loss)))
         return g, loss.value
@@ -513,9 +528,9 @@ class Surrogate:
         n = x.shape[0]
         if out is None:
             out = torch.empty(n, dtype=torch.float32, device="cuda")
-        _enter(self.stream, x, out)
+        cur = _enter(self.stream, x, out, event=self._event)
         _check(_lib.sg_predict(self.handle, ctypes.c_void_p(x.data_ptr()), n, ctypes.c_void_p(out.data_ptr())))
-        _leave(self.stream)
+        _leave(self.stream, cur, self._done)
         return out
 
     def sync(self):
