@@ -21,13 +21,24 @@ constexpr int HMAX = 2000;       // halo nodes beyond which no chunk fits: 4 * (
 constexpr int HSORT = 2048;
 constexpr int STEP = 64;         // chunk starts and cuts are multiples of this
 
+// Tiles run x fastest, then along y within a band of BAND tile rows, then
+// along z, then over the bands: the chunks that an XCD has in flight form a
+// box, and more of each other's halo is still in its L2. With tiles of
+// 32 x 8 x 4 instead of 32 x 4 x 4 in plain x, y, z order: a step of 16 species
+// on 256^3 1,827 -> 1,776 us, HBM traffic of a launch 7.98 -> 7.68 GB (bands
+// alone: 2, 3, 4, 6, 8 rows 1,832, 1,815, 1,812, 1,810, 1,806 us).
+constexpr int BAND = 4;
+
 struct Order {  // lattice and ordering tiles
-    int nx, ny, nz, tx, ty, tz, ntx, nty;
+    int nx, ny, nz, tx, ty, tz, ntx, nty, ntz;
 };
 
 // Lattice index of position p (x fastest) of ordering tile b, -1 outside the lattice.
 __device__ __forceinline__ int64_t tile_node(const Order& o, int64_t b, int p) {
-    const int bx = (int)(b % o.ntx), by = (int)((b / o.ntx) % o.nty), bz = (int)(b / ((int64_t)o.ntx * o.nty));
+    const int64_t per = (int64_t)BAND * o.ntz * o.ntx;  // tiles of a whole band
+    const int bd = (int)(b / per), rows = min(BAND, o.nty - bd * BAND);
+    const int r = (int)((b - bd * per) / o.ntx), bx = (int)((b - bd * per) % o.ntx);
+    const int by = bd * BAND + r % rows, bz = r / rows;
     const int lx = p % o.tx, ly = (p / o.tx) % o.ty, lz = p / (o.tx * o.ty);
     const int x = bx * o.tx + lx, y = by * o.ty + ly, z = bz * o.tz + lz;
     return x < o.nx && y < o.ny && z < o.nz ? x + (int64_t)o.nx * (y + (int64_t)o.ny * z) : -1;
@@ -272,10 +283,12 @@ lbmp_status build_chunks(const lbmp_flow* f, const int tile[3], int CH, int zslo
                          size_t scratch_bytes, const ChunkTables& T, hipStream_t s, int64_t* nch) {
     *nch = 0;
     const int64_t NF = f->nf;
-    Order o{f->nx, f->ny, f->nz, std::min(tile[0], f->nx), std::min(tile[1], f->ny), std::min(tile[2], f->nz), 0, 0};
+    Order o{f->nx, f->ny, f->nz, std::min(tile[0], f->nx), std::min(tile[1], f->ny), std::min(tile[2], f->nz),
+            0, 0, 0};
     o.ntx = (o.nx + o.tx - 1) / o.tx;
     o.nty = (o.ny + o.ty - 1) / o.ty;
-    const int64_t nt = (int64_t)o.ntx * o.nty * ((o.nz + o.tz - 1) / o.tz), nb = (NF + STEP - 1) / STEP;
+    o.ntz = (o.nz + o.tz - 1) / o.tz;
+    const int64_t nt = (int64_t)o.ntx * o.nty * o.ntz, nb = (NF + STEP - 1) / STEP;
     if (CH > CT || CH * cap > (int64_t)INT32_MAX) return LBMP_OK;  // not offered
     Carver c(scratch, scratch_bytes);
     uint32_t* cf = c.take<uint32_t>(nt);

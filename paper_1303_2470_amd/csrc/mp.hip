@@ -1392,7 +1392,7 @@ __global__ void __launch_bounds__(NH * BLK) __attribute__((amdgpu_waves_per_eu(4
 
 // ------------------------------------------------------------------ gathered chunks
 // Variant 8: a block updates one chunk of up to GCH fluid nodes that are
-// consecutive in the compact storage, whose order (tiles of 32 x 4 x 4 lattice
+// consecutive in the compact storage, whose order (tiles of 32 x 8 x 4 lattice
 // nodes, fluid nodes in lattice order within a tile) keeps a chunk spatially
 // compact. Per field the buffer unit copies, in 16-byte quads (4 consecutive
 // compact values, one quad per thread), the chunk's own values (one
@@ -1412,7 +1412,7 @@ struct GatherShape {
     static constexpr int ZSLOT = REG - 1;                 // in the last quad, never copied: reads 0
 };
 constexpr int GCH = 2 * BLK;                     // the largest chunk
-constexpr int GTX = 32, GTY = 4, GTZ = 4;        // ordering tiles (compact storage)
+constexpr int GTX = 32, GTY = 8, GTZ = 4;        // ordering tiles (compact storage)
 
 template <int NH>
 __global__ void __launch_bounds__(NH * BLK) __attribute__((amdgpu_waves_per_eu(4))) k_mp_gather(
@@ -2266,7 +2266,7 @@ struct GeomHost {
     int32_t* fidx;  // [N] index of a fluid node among the fluid nodes in lattice order, -1 on solid
     int32_t* fnode; // [nf] lattice index of a fluid node
     // gathered chunks (variant 8): the compact order of their fields (gidx,
-    // tiles of 32 x 4 x 4 nodes), chunk table, halo quads, neighbour slots, lattice
+    // tiles of 32 x 8 x 4 nodes), chunk table, halo quads, neighbour slots, lattice
     // index and adsorbed-field index per compact node, adsorbed-field index
     // per interface slot (aperm); built when the variant is chosen or timed
     int32_t *gidx, *gnode, *gaslot, *ghsrc, *aperm;
