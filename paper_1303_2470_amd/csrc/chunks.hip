@@ -242,7 +242,7 @@ __global__ void __launch_bounds__(CT) k_chunk_len(Order o, const int32_t* __rest
 // Tables of chunk c = list[c] (first node, nodes).
 __global__ void __launch_bounds__(CT) k_chunk_build(Order o, const int32_t* __restrict__ gnode,
                                                     const int32_t* __restrict__ gidx, const int2* __restrict__ list,
-                                                    int64_t NF, int CH, int zslot, int4* __restrict__ gch,
+                                                    int64_t NF, int CH, int4* __restrict__ gch,
                                                     int32_t* __restrict__ ghsrc, uint16_t* __restrict__ gnbr) {
     __shared__ Halo h;
     __shared__ int hq[CT];
@@ -257,12 +257,13 @@ __global__ void __launch_bounds__(CT) k_chunk_build(Order o, const int32_t* __re
         }
     if (tid == 0) gch[blockIdx.x] = make_int4(base, C, (int)hoff, H);
     __syncthreads();
-    if (tid >= C) return;
     const int Cq = (C + 3) / 4;
-    const Pull p(o, gnode[base + tid]);
+    const int nz = min(32, 4 * (CH - Cq - H));  // zero slots to choose from: the region's last ones, 4 or more
+    const uint32_t zeros = 0xffffffffu << (32 - nz);
+    const Pull p(o, gnode[base + min(tid, C - 1)]);
     for (int k = 0; k < NL; ++k) {
-        const int32_t j = p.at(o, gidx, k);
-        int sl = zslot;
+        const int32_t j = tid < C ? p.at(o, gidx, k) : -1;
+        int sl = -1;
         if (j >= base && j < base + C) sl = j - base;
         else if (j >= 0) {
             int lo = 0, hi = nh - 1;  // j is one of hs
@@ -273,13 +274,24 @@ __global__ void __launch_bounds__(CT) k_chunk_build(Order o, const int32_t* __re
             const int q = h.qi[lo];
             sl = 4 * (Cq + q) + (j - hq[q]);
         }
-        gnbr[(int64_t)k * NF + base + tid] = (uint16_t)sl;
+        // A link from a solid node reads a slot that the copy leaves at zero.
+        // The step kernel's arrival reads are bound by bank conflicts, and one
+        // zero for all of them met another lane's bank in nearly every read
+        // (3.95 cycles a read, counted over this table as 32 lanes on 32 banks;
+        // 2 without conflicts): a zero in a bank that no other lane of the
+        // half-wave reads serves all of its solid links (3.36). 256^3, 16
+        // species: conflicts 3.26e8 -> 2.37e8 cycles, 1,776 -> 1,746 us a step.
+        uint32_t used = sl >= 0 ? 1u << (sl & 31) : 0u;
+        for (int m = 1; m < 32; m <<= 1) used |= __shfl_xor(used, m, 64);
+        const uint32_t free = zeros & ~used;
+        if (sl < 0) sl = 4 * CH - 1 - (free ? __clz(free) : 0);
+        if (tid < C) gnbr[(int64_t)k * NF + base + tid] = (uint16_t)sl;
     }
 }
 
 }  // namespace
 
-lbmp_status build_chunks(const lbmp_flow* f, const int tile[3], int CH, int zslot, int64_t cap, void* scratch,
+lbmp_status build_chunks(const lbmp_flow* f, const int tile[3], int CH, int64_t cap, void* scratch,
                          size_t scratch_bytes, const ChunkTables& T, hipStream_t s, int64_t* nch) {
     *nch = 0;
     const int64_t NF = f->nf;
@@ -313,7 +325,7 @@ lbmp_status build_chunks(const lbmp_flow* f, const int tile[3], int CH, int zslo
         base += C;
     }
     LBMP_HIP(hipMemcpyAsync(list, ch.data(), ch.size() * sizeof(int2), hipMemcpyHostToDevice, s));
-    k_chunk_build<<<(unsigned)ch.size(), CT, 0, s>>>(o, T.gnode, T.gidx, list, NF, CH, zslot, T.gch, T.ghsrc, T.gnbr);
+    k_chunk_build<<<(unsigned)ch.size(), CT, 0, s>>>(o, T.gnode, T.gidx, list, NF, CH, T.gch, T.ghsrc, T.gnbr);
     LBMP_HIP(hipGetLastError());
     LBMP_HIP(hipStreamSynchronize(s));  // ch is read by the copy
     *nch = (int64_t)ch.size();

@@ -112,6 +112,6 @@ struct ChunkTables {
 // Ordering tiles of tile[0..2] nodes, chunks of up to CH nodes (a multiple of
 // 64, at most 512), at most cap of them; ghsrc holds CH quads per chunk.
 // *nch = 0 when some chunk does not fit even cut short.
-lbmp_status build_chunks(const lbmp_flow* f, const int tile[3], int CH, int zslot, int64_t cap, void* scratch,
+lbmp_status build_chunks(const lbmp_flow* f, const int tile[3], int CH, int64_t cap, void* scratch,
                          size_t scratch_bytes, const ChunkTables& T, hipStream_t s, int64_t* nch);
 }  // namespace lbmp

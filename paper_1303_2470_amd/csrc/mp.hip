@@ -2727,9 +2727,8 @@ lbmp_status build_gather(lbmp_mp* h) {
         if (g.gather_built) continue;
         g.gnh = 2;
         if (const char* e = getenv("LBMP_GATHER_NH")) g.gnh = atoi(e) == 1 ? 1 : 2;
-        const int zs = g.gnh == 1 ? GatherShape<1>::ZSLOT : GatherShape<2>::ZSLOT;
         const ChunkTables T{g.gidx, g.gnode, g.gaslot, g.ghsrc, g.aperm, g.gch, g.gnbr};
-        lbmp_status st = build_chunks(g.flow, tile, g.gnh * BLK, zs, gather_chunk_cap(g.nf), h->setup_tmp,
+        lbmp_status st = build_chunks(g.flow, tile, g.gnh * BLK, gather_chunk_cap(g.nf), h->setup_tmp,
                                       (size_t)setup_doubles(g.N) * 8, T, h->stream, &g.nch);
         if (st != LBMP_OK) return st;
         g.gather_built = true;
