@@ -900,15 +900,21 @@ struct DmaShape {
     // (NPL hy + pz) RXS + hx, so the 19 stencil values of a node lie within
     // (2 NPL + 2) RXS + 3 dwords of its (x-1, y-1, z-1) corner.
     __host__ __device__ static constexpr int at(int hy, int pz, int hx) { return (NPL * hy + pz) * RXS + hx; }
-    // vector-memory operations a wave issues after a field's copy, up to the
-    // wait for it: the copies of the next two fields and the stores of the
-    // three before (with and without interface nodes in the wave; a field's
-    // copy goes out right after the barrier three fields earlier, before that
-    // field's update and store)
-    static constexpr int WAIT_I = 2 * (NCP + 1) + 3 * 2, WAIT_N = 2 * NCP + 3;
-    // waves without a node to update (lane compaction) copy and store nothing else
-    static constexpr int WAIT_IDLE = 2 * NCP;
 };
+
+// Vector-memory operations a wave issues after the copy of quantity q's field,
+// up to the wait for it: the copies of the next two fields and the stores of
+// the three before (a field's copy goes out right after the barrier three
+// fields earlier, before that field's update and store); fewer at a block's
+// first three and last two fields. ncp: a field's region copies; the adsorbed
+// values are one more copy and store where the wave has interface nodes; an
+// idle wave stores nothing. (The store of a block sum is left out: it makes
+// the wait for one operation more.) Waiting for every copy at those five
+// fields instead exposed two memory latencies a block.
+__host__ __device__ constexpr int fields_wait(int ncp, bool anyi, bool idle, bool first, bool last, int q) {
+    const int copies = last && q >= 2 ? 3 - q : 2, stores = first && q < 3 ? q : 3;
+    return copies * (ncp + (anyi ? 1 : 0)) + (idle ? 0 : stores * (anyi ? 2 : 1));
+}
 constexpr int DMA_GMAX = 64;                     // species per block
 constexpr int NSUM = 5;                          // per-node block sums of a species
 
@@ -1238,9 +1244,8 @@ __global__ void __launch_bounds__(NH * BLK) __attribute__((amdgpu_waves_per_eu(4
     using T_ = std::true_type;
     using F_ = std::false_type;
     // anyc: the wave has interface nodes (wave-uniform; both paths pass the
-    // same barriers). firstc / lastc: the block's first / last species, whose
-    // first / last two fields wait for every copy in flight (fewer operations
-    // follow their copies than the steady-state wait counts assume).
+    // same barriers). firstc / lastc: the block's first / last species (fewer
+    // operations follow the copies of their first / last fields).
     auto run = [&](auto anyc, auto idlec) {
         constexpr bool ANYI = decltype(anyc)::value;
         constexpr bool IDLE = decltype(idlec)::value;  // no node in the wave: no update, no stores
@@ -1274,14 +1279,8 @@ __global__ void __launch_bounds__(NH * BLK) __attribute__((amdgpu_waves_per_eu(4
                 constexpr int q = decltype(qc)::value;
                 const int f = 4 * s + q;
                 // field f has landed for the whole block once this wave has at
-                // most the operations issued after it outstanding: the loads of
-                // f+1, f+2 and the stores of f-3, f-2, f-1 (2 (NCP + 1) + 3 * 2
-                // with interface nodes in the wave, 2 NCP + 3 without); the
-                // block's first three and last two fields have fewer behind them
-                if constexpr ((FIRST && q < 3) || (LAST && q >= 2)) barrier_vm0();
-                else if constexpr (IDLE) barrier_vm<SH::WAIT_IDLE>();
-                else if constexpr (ANYI) barrier_vm<SH::WAIT_I>();
-                else barrier_vm<SH::WAIT_N>();
+                // most the operations issued after it outstanding
+                barrier_vm<fields_wait(NCP, ANYI, IDLE, FIRST, LAST, q)>();
                 if constexpr (q == 0) {
                     finish(pend2);
                     pend2 = -1;
@@ -1425,7 +1424,6 @@ __global__ void __launch_bounds__(NH * BLK) __attribute__((amdgpu_waves_per_eu(4
     constexpr int DBLK = GS::DBLK, NCP = 1, REGION = GS::REG, STAGE = GS::REG + DBLK;
     constexpr int GZSLOT = GS::ZSLOT;
     constexpr int NW = DBLK / 64;
-    constexpr int WAIT_I = 2 * (NCP + 1) + 3 * 2, WAIT_N = 2 * NCP + 3, WAIT_IDLE = 2 * NCP;
     __shared__ __align__(16) float st0[STAGE];
     __shared__ __align__(16) float st1[STAGE];
     __shared__ __align__(16) float st2[STAGE];
@@ -1564,10 +1562,7 @@ __global__ void __launch_bounds__(NH * BLK) __attribute__((amdgpu_waves_per_eu(4
             auto field = [&](auto qc) {
                 constexpr int q = decltype(qc)::value;
                 const int f = 4 * s + q;
-                if constexpr ((FIRST && q < 3) || (LAST && q >= 2)) barrier_vm0();
-                else if constexpr (IDLE) barrier_vm<WAIT_IDLE>();
-                else if constexpr (ANYI) barrier_vm<WAIT_I>();
-                else barrier_vm<WAIT_N>();
+                barrier_vm<fields_wait(NCP, ANYI, IDLE, FIRST, LAST, q)>();
                 if constexpr (q == 0) {
                     finish(pend2);
                     pend2 = -1;
