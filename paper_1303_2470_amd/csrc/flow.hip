@@ -21,9 +21,12 @@ namespace lbmp {
 // Populations are stored in tiles of PT nodes, [tile][19][PT]: a block reads
 // and writes one stretch of memory instead of 19 (+ 19) that lie N_F values
 // apart (256^3 porous medium: 503 -> 467 us a step; tiles of 64 to 4,096 nodes
-// within 1 %).
-constexpr int PT = 256;
-__host__ __device__ constexpr int64_t tiled(int64_t nf) { return (nf + PT - 1) / PT * PT; }
+// within 1 %). PT = 1, node by node, needs no room for a last tile that is not
+// full: for the resident kernel, which loads them once per launch, and for a
+// scratch that has no such room.
+constexpr int TILE = 256;
+__host__ __device__ constexpr int64_t tiled(int64_t nf) { return (nf + TILE - 1) / TILE * TILE; }
+template <int PT>
 __device__ __forceinline__ int64_t pidx(int k, int64_t i) { return (i / PT * 19 + k) * PT + i % PT; }
 
 struct BGKParams {
@@ -94,6 +97,7 @@ __device__ inline void bgk_collide(double f[19], const BGKParams& P, double& rho
 
 // Start at rest: equilibrium with rho = 1, u = 0, then one collision with the
 // force (the same for every node).
+template <int PT>
 __global__ void k_bgk_init(double* __restrict__ fo, int64_t NF, BGKParams P, double* __restrict__ u0) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= NF) return;
@@ -103,7 +107,7 @@ __global__ void k_bgk_init(double* __restrict__ fo, int64_t NF, BGKParams P, dou
     for (int k = 0; k < NL; ++k) f[k + 1] = lw(k);
     double rho, ux, uy, uz;
     bgk_collide(f, P, rho, ux, uy, uz);
-    for (int k = 0; k < 19; ++k) fo[pidx(k, i)] = f[k];
+    for (int k = 0; k < 19; ++k) fo[pidx<PT>(k, i)] = f[k];
     u0[i] = ux;
     u0[NF + i] = uy;
     u0[2 * NF + i] = uz;
@@ -141,7 +145,7 @@ __global__ void k_bgk_table(const int32_t* __restrict__ gnode, const int32_t* __
 #pragma unroll
     for (int k = 0; k < NL; ++k) {
         const int32_t j = up.at(gidx, k);
-        pull[k * NF + i] = (int32_t)(j < 0 ? pidx((k ^ 1) + 1, i) : pidx(k + 1, j));
+        pull[k * NF + i] = (int32_t)(j < 0 ? pidx<TILE>((k ^ 1) + 1, i) : pidx<TILE>(k + 1, j));
     }
 }
 
@@ -154,7 +158,7 @@ __global__ void k_bgk_table(const int32_t* __restrict__ gnode, const int32_t* __
 // copy reaches 4.9-5.2 (540 us before the tiles, the remap and the shorter
 // collision). Small ones, held by the last-level
 // cache, are bound by its bandwidth and by the chain of dependent loads.
-template <bool TAB>
+template <bool TAB, int PT>
 __global__ void __launch_bounds__(256) k_bgk_step(const int32_t* __restrict__ gnode, const int32_t* __restrict__ gidx,
                                                   const int32_t* __restrict__ pull, const double* __restrict__ fi,
                                                   double* __restrict__ fo, int64_t NF, int nx, int ny, int nz,
@@ -164,7 +168,7 @@ __global__ void __launch_bounds__(256) k_bgk_step(const int32_t* __restrict__ gn
     const int64_t i = blk * blockDim.x + threadIdx.x;
     if (i >= NF) return;
     double f[19];
-    f[0] = fi[pidx(0, i)];
+    f[0] = fi[pidx<PT>(0, i)];
     if constexpr (TAB) {
         int32_t at[NL];
 #pragma unroll
@@ -176,13 +180,13 @@ __global__ void __launch_bounds__(256) k_bgk_step(const int32_t* __restrict__ gn
 #pragma unroll
         for (int k = 0; k < NL; ++k) {
             const int32_t j = up.at(gidx, k);
-            f[k + 1] = fi[j < 0 ? pidx((k ^ 1) + 1, i) : pidx(k + 1, (uint32_t)j)];
+            f[k + 1] = fi[j < 0 ? pidx<PT>((k ^ 1) + 1, i) : pidx<PT>(k + 1, (uint32_t)j)];
         }
     }
     double rho, ux, uy, uz;
     bgk_collide(f, P, rho, ux, uy, uz);
 #pragma unroll
-    for (int k = 0; k < 19; ++k) fo[pidx(k, i)] = f[k];
+    for (int k = 0; k < 19; ++k) fo[pidx<PT>(k, i)] = f[k];
     if (uout) {
         uout[i] = ux;
         uout[NF + i] = uy;
@@ -223,7 +227,7 @@ __global__ void __launch_bounds__(BS) k_bgk_resident(const int32_t* __restrict__
     }
     // lanes without a node carry the state at rest along
 #pragma unroll
-    for (int k = 0; k < 19; ++k) pop[k * BS + i] = act ? F[pidx(k, i)] : (k == 0 ? W_REST : lw(k - 1));
+    for (int k = 0; k < 19; ++k) pop[k * BS + i] = act ? F[pidx<1>(k, i)] : (k == 0 ? W_REST : lw(k - 1));
     // velocities of the last step (slot step0 % 3) and the one before
     const int s0 = (int)(step0 % 3);
     double ua[3], ub[3], uc[3];
@@ -291,7 +295,7 @@ __global__ void __launch_bounds__(BS) k_bgk_resident(const int32_t* __restrict__
     const int s1 = (int)((step0 + done) % 3);
     if (act) {
 #pragma unroll
-        for (int k = 0; k < 19; ++k) F[pidx(k, i)] = pop[k * BS + i];
+        for (int k = 0; k < 19; ++k) F[pidx<1>(k, i)] = pop[k * BS + i];
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
             U[s1][d * NF + i] = ua[d];
@@ -377,10 +381,13 @@ constexpr int RES_BLOCKS = 512;
 // beyond (499 k nodes: 29.1 against 28.4).
 constexpr int64_t TABLE_NODES = 3 << 16;
 
-// what a solve needs, and the pull table on top of it
+// what a solve needs; room for full tiles and the pull table on top of it
 static size_t scratch_bytes_for(int64_t N) {
     return 2 * align_up(19 * 8 * (size_t)N) + 3 * align_up(24 * (size_t)N) +
            align_up(2 * 8 * RES_BLOCKS) + align_up(16) + 2 * align_up(4 * (size_t)N);
+}
+static size_t tile_bytes_for(int64_t NF) {
+    return 2 * (align_up(19 * 8 * (size_t)tiled(NF)) - align_up(19 * 8 * (size_t)NF));
 }
 static size_t table_bytes_for(int64_t NF) { return align_up(4 * NL * (size_t)NF); }
 
@@ -394,7 +401,7 @@ extern "C" lbmp_status lb_flow_workspace_bytes(const lbmp_geometry* g, size_t* p
         return fail(LBMP_EINVAL, "invalid geometry");
     int64_t N = (int64_t)g->nx * g->ny * g->nz;
     if (persistent) *persistent = align_up(sizeof(lbmp_flow)) + geometry_bytes(N);
-    if (scratch_out) *scratch_out = scratch_bytes_for(N) + (N <= TABLE_NODES ? table_bytes_for(N) : 0);
+    if (scratch_out) *scratch_out = scratch_bytes_for(N) + tile_bytes_for(N) + (N <= TABLE_NODES ? table_bytes_for(N) : 0);
     return LBMP_OK;
 }
 
@@ -456,8 +463,13 @@ static lbmp_status flow_solve(const lbmp_geometry* g, double tau, const double f
     if (st != LBMP_OK) return st;
     const int64_t N = f->N, NF = f->nf, n3 = 3 * NF;
     Carver c(dev_scratch, scratch_bytes);
-    double* fa = c.take<double>(19 * tiled(NF));
-    double* fb = c.take<double>(19 * tiled(NF));
+    const bool resident = NF <= BRES_NODES;
+    // (U, part, res, gidx and gnode take what scratch_bytes_for counts, for NF
+    // fluid nodes of N)
+    const bool tiles = !resident && scratch_bytes_for(NF) + 2 * (align_up(4 * (size_t)N) - align_up(4 * (size_t)NF)) +
+                                        tile_bytes_for(NF) <= scratch_bytes;
+    double* fa = c.take<double>(19 * (tiles ? tiled(NF) : NF));
+    double* fb = c.take<double>(19 * (tiles ? tiled(NF) : NF));
     // velocities of the last three steps, slot = step % 3
     double* U[3] = {c.take<double>(n3), c.take<double>(n3), c.take<double>(n3)};
     double* part = c.take<double>(2 * RES_BLOCKS);
@@ -466,12 +478,12 @@ static lbmp_status flow_solve(const lbmp_geometry* g, double tau, const double f
     int32_t* gnode = c.take<int32_t>(N);
     rank_fluid(f, gidx, gnode, s);
     const unsigned nbf = (unsigned)((NF + 255) / 256);
-    const bool resident = NF <= BRES_NODES;
-    const bool tab = !resident && NF <= TABLE_NODES && c.off + table_bytes_for(NF) <= scratch_bytes;
+    const bool tab = tiles && NF <= TABLE_NODES && c.off + table_bytes_for(NF) <= scratch_bytes;
     int32_t* const pull = tab ? c.take<int32_t>(NL * NF) : nullptr;
     if (tab) k_bgk_table<<<nbf, 256, 0, s>>>(gnode, gidx, NF, f->nx, f->ny, f->nz, pull);
     BGKParams P{1.0 / tau, 1.0 - 0.5 / tau, force[0], force[1], force[2]};
-    k_bgk_init<<<nbf, 256, 0, s>>>(fa, NF, P, U[0]);
+    if (tiles) k_bgk_init<TILE><<<nbf, 256, 0, s>>>(fa, NF, P, U[0]);
+    else k_bgk_init<1><<<nbf, 256, 0, s>>>(fa, NF, P, U[0]);
     // before step 2 the history holds the start only
     LBMP_HIP(hipGetLastError());
     double resv = INFINITY;
@@ -516,8 +528,13 @@ static lbmp_status flow_solve(const lbmp_geometry* g, double tau, const double f
         // last two steps (the reported velocity)
         const bool need = check || ((sn + 1) % ce) == 0 || ((sn + 2) % ce) == 0 || sn + 1 >= max_steps;
         double* uo = need ? U[sn % 3] : nullptr;
-        if (tab) k_bgk_step<true><<<nbf, 256, 0, s>>>(gnode, gidx, pull, fa, fb, NF, f->nx, f->ny, f->nz, P, uo);
-        else k_bgk_step<false><<<nbf, 256, 0, s>>>(gnode, gidx, pull, fa, fb, NF, f->nx, f->ny, f->nz, P, uo);
+        auto go = [&](auto tabc, auto ptc) {
+            k_bgk_step<decltype(tabc)::value, decltype(ptc)::value>
+                <<<nbf, 256, 0, s>>>(gnode, gidx, pull, fa, fb, NF, f->nx, f->ny, f->nz, P, uo);
+        };
+        if (tab) go(std::true_type(), std::integral_constant<int, TILE>());
+        else if (tiles) go(std::false_type(), std::integral_constant<int, TILE>());
+        else go(std::false_type(), std::integral_constant<int, 1>());
         std::swap(fa, fb);
         step = sn;
         if (check) {

@@ -77,3 +77,40 @@ def test_long_solves_cross_launches(lb):
     ref = oracle.bgk(m, 1.0, [1e-7, 0, 0], 1e-10, 400000)
     assert f.converged and f.steps == ref["steps"] and f.steps > 20000
     f.free()
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 300), (11, 11, 11), (9, 31, 7), (59, 59, 59)])  # nz, ny, nx
+def test_scratch_of_the_least_size(lb, shape):
+    """A lattice without solid nodes leaves the populations no room to spare in
+    the least scratch a solve accepts: nothing behind it is written, and the
+    velocities are those of a solve with all the scratch the query asks for."""
+    import ctypes
+    import torch
+    mask = np.zeros(shape, dtype=np.uint8)
+    args = dict(tol=0.0, max_steps=60, allow_unconverged=True)
+    ref = lb.lb_flow_solve(mask, 0.8, (1e-6, 2e-6, -1e-6), **args)
+    n = mask.size
+    up = lambda b: -(-b // 256) * 256
+    least = 2 * up(152 * n) + 3 * up(24 * n) + up(16 * 512) + up(16) + 2 * up(4 * n)
+    lib, (g, m) = lb.load_library(), lb._geometry(mask, (1, 1, 1), 18)
+    pb, sb = ctypes.c_size_t(), ctypes.c_size_t()
+    assert lib.lb_flow_workspace_bytes(ctypes.byref(g), ctypes.byref(pb), ctypes.byref(sb)) == 0
+    assert sb.value >= least
+    ws = torch.empty(pb.value, dtype=torch.uint8, device="cuda")
+    scratch = torch.full((least + (1 << 20),), 0xA5, dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    stream, f = torch.cuda.Stream(), (ctypes.c_double * 3)(1e-6, 2e-6, -1e-6)
+    h, steps, res = ctypes.c_void_p(), ctypes.c_int64(), ctypes.c_double()
+
+    def solve(size):
+        return lib.lb_flow_solve(ctypes.byref(g), 0.8, f, 0.0, 60, 100, ctypes.c_void_p(ws.data_ptr()), pb.value,
+                                 ctypes.c_void_p(scratch.data_ptr()), size, ctypes.c_void_p(stream.cuda_stream),
+                                 ctypes.byref(h), ctypes.byref(steps), ctypes.byref(res))
+    assert solve(least - 1) == -3  # refused
+    assert solve(least) == -4      # 60 steps to a tolerance of 0: not converged
+    flow = lb.Flow(h, ws, m, g, stream, steps.value, res.value, False)
+    torch.cuda.synchronize()
+    assert bool((scratch[least:] == 0xA5).all())
+    assert np.array_equal(flow.velocity(), ref.velocity())
+    flow.free()
+    ref.free()
