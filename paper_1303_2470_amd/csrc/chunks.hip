@@ -23,10 +23,11 @@ constexpr int STEP = 64;         // chunk starts and cuts are multiples of this
 
 // Tiles run x fastest, then along y within a band of BAND tile rows, then
 // along z, then over the bands: the chunks that an XCD has in flight form a
-// box, and more of each other's halo is still in its L2. With tiles of
-// 32 x 8 x 4 instead of 32 x 4 x 4 in plain x, y, z order: a step of 16 species
-// on 256^3 1,827 -> 1,776 us, HBM traffic of a launch 7.98 -> 7.68 GB (bands
-// alone: 2, 3, 4, 6, 8 rows 1,832, 1,815, 1,812, 1,810, 1,806 us).
+// box, and more of each other's halo is still in its L2. A step of 16 species
+// on 256^3, tiles of 32 x 4 x 4: 1,827 us and 7.98 GB of HBM traffic in plain
+// x, y, z order, 1,812 us and 7.68 GB in bands of 4 (2, 3, 6, 8 rows: 1,832,
+// 1,815, 1,810, 1,806 us). Tiles of 32 x 8 x 4 have shorter halos, fewer
+// copies: 1,776 us, though 8.06 GB.
 constexpr int BAND = 4;
 
 struct Order {  // lattice and ordering tiles
