@@ -7,9 +7,8 @@
 // On the host (one core, a sort per chunk) they took 40 ms for a 64^3 medium
 // and were most of a short run; here a chunk is one block, whose halo is
 // deduplicated in an LDS hash table and sorted there.
-#include <vector>
-
 #include "lbmp_internal.hpp"
+#include "plan.hpp"
 
 namespace lbmp {
 namespace {
@@ -19,31 +18,6 @@ constexpr int CT = 512;          // threads per chunk
 constexpr int HTAB = 4096;       // hash slots of a chunk's halo
 constexpr int HMAX = 2000;       // halo nodes beyond which no chunk fits: 4 * (511 - 64 / 4) = 1,980 at its shortest
 constexpr int HSORT = 2048;
-constexpr int STEP = 64;         // chunk starts and cuts are multiples of this
-
-// Tiles run x fastest, then along y within a band of BAND tile rows, then
-// along z, then over the bands: the chunks that an XCD has in flight form a
-// box, and more of each other's halo is still in its L2. A step of 16 species
-// on 256^3, tiles of 32 x 4 x 4: 1,827 us and 7.98 GB of HBM traffic in plain
-// x, y, z order, 1,812 us and 7.68 GB in bands of 4 (2, 3, 6, 8 rows: 1,832,
-// 1,815, 1,810, 1,806 us). Tiles of 32 x 8 x 4 have shorter halos, fewer
-// copies: 1,776 us, though 8.06 GB.
-constexpr int BAND = 4;
-
-struct Order {  // lattice and ordering tiles
-    int nx, ny, nz, tx, ty, tz, ntx, nty, ntz;
-};
-
-// Lattice index of position p (x fastest) of ordering tile b, -1 outside the lattice.
-__device__ __forceinline__ int64_t tile_node(const Order& o, int64_t b, int p) {
-    const int64_t per = (int64_t)BAND * o.ntz * o.ntx;  // tiles of a whole band
-    const int bd = (int)(b / per), rows = min(BAND, o.nty - bd * BAND);
-    const int r = (int)((b - bd * per) / o.ntx), bx = (int)((b - bd * per) % o.ntx);
-    const int by = bd * BAND + r % rows, bz = r / rows;
-    const int lx = p % o.tx, ly = (p / o.tx) % o.ty, lz = p / (o.tx * o.ty);
-    const int x = bx * o.tx + lx, y = by * o.ty + ly, z = bz * o.tz + lz;
-    return x < o.nx && y < o.ny && z < o.nz ? x + (int64_t)o.nx * (y + (int64_t)o.ny * z) : -1;
-}
 
 // Fluid and interfacial nodes of every ordering tile.
 __global__ void __launch_bounds__(TT) k_tile_count(const int8_t* __restrict__ cls, Order o, uint32_t* __restrict__ cf,
@@ -231,12 +205,12 @@ __global__ void __launch_bounds__(CT) k_chunk_len(Order o, const int32_t* __rest
     int C = min(CH, NF - base), nh;
     for (;;) {
         const int H = chunk_halo(h, o, gnode, gidx, base, C, nh);
-        const bool fits = H >= 0 && (C + 3) / 4 + H <= CH - 1;
+        const bool fits = H >= 0 && chunk_fits(C, H, CH);
         if (fits || C <= STEP) {
             if (threadIdx.x == 0) len[blockIdx.x] = fits ? C : 0;
             return;
         }
-        C = max(STEP, C - STEP);
+        C = shorter_chunk(C);
     }
 }
 
@@ -296,11 +270,7 @@ lbmp_status build_chunks(const lbmp_flow* f, const int tile[3], int CH, int64_t 
                          size_t scratch_bytes, const ChunkTables& T, hipStream_t s, int64_t* nch) {
     *nch = 0;
     const int64_t NF = f->nf;
-    Order o{f->nx, f->ny, f->nz, std::min(tile[0], f->nx), std::min(tile[1], f->ny), std::min(tile[2], f->nz),
-            0, 0, 0};
-    o.ntx = (o.nx + o.tx - 1) / o.tx;
-    o.nty = (o.ny + o.ty - 1) / o.ty;
-    o.ntz = (o.nz + o.tz - 1) / o.tz;
+    const Order o = make_order(f->nx, f->ny, f->nz, tile[0], tile[1], tile[2]);
     const int64_t nt = (int64_t)o.ntx * o.nty * o.ntz, nb = (NF + STEP - 1) / STEP;
     if (CH > CT || CH * cap > (int64_t)INT32_MAX) return LBMP_OK;  // not offered
     Carver c(scratch, scratch_bytes);
@@ -318,13 +288,9 @@ lbmp_status build_chunks(const lbmp_flow* f, const int tile[3], int CH, int64_t 
     std::vector<int32_t> lh(nb);
     LBMP_HIP(hipMemcpyAsync(lh.data(), len, nb * 4, hipMemcpyDeviceToHost, s));
     LBMP_HIP(hipStreamSynchronize(s));
-    std::vector<int2> ch;
-    for (int64_t base = 0; base < NF;) {
-        const int C = lh[base / STEP];
-        if (C == 0 || (int64_t)ch.size() >= cap) return LBMP_OK;  // does not fit: not offered
-        ch.push_back(make_int2((int)base, C));
-        base += C;
-    }
+    const std::vector<ChunkSpan> ch = chunk_spans(lh.data(), NF, cap);
+    if (ch.empty()) return LBMP_OK;  // does not fit: not offered
+    static_assert(sizeof(ChunkSpan) == sizeof(int2), "copied as int2");
     LBMP_HIP(hipMemcpyAsync(list, ch.data(), ch.size() * sizeof(int2), hipMemcpyHostToDevice, s));
     k_chunk_build<<<(unsigned)ch.size(), CT, 0, s>>>(o, T.gnode, T.gidx, list, NF, CH, T.gch, T.ghsrc, T.gnbr);
     LBMP_HIP(hipGetLastError());
