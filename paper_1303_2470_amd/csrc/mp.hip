@@ -247,13 +247,15 @@ struct Red {
 
 // Block b of the n1 + n2: a chunk (b < n1) of the partials of time t - 1, or
 // the sums of one pair at time t - 1 (t - 2 with chunks) into its series and
-// the watchdog. Fixed order: entries of a pair are one flat array, thread i
-// adds entries i, i + blockDim, ... (all of sum i % NRED) into eight
-// accumulators, and the threads of each sum are added by a fixed tree.
+// the watchdog. Fixed order, the same in every launch whatever its blocks
+// (a step's sums must not depend on where a run is split into calls): entries
+// of a pair are one flat array, thread i < BLK adds entries i, i + BLK, ...
+// (all of sum i % NRED) into eight accumulators, and the threads of each sum
+// are added by a fixed tree; the other threads of a larger block only wait.
 template <typename T>
 __device__ __forceinline__ void series_block(const GeomDev<T>* __restrict__ geoms, const Red& R, int b) {
-    __shared__ double wsum[16][NRED];
-    const int tid = threadIdx.x, BD = blockDim.x, lane = tid & 63, wv = tid >> 6, nwv = BD / 64;
+    __shared__ double wsum[BLK / 64][NRED];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int64_t t = R.ctl->t + R.dt;
     const bool first = b < R.n1;
     const int w = first ? b / R.nch : b - R.n1, c = first ? b % R.nch : 0;
@@ -272,30 +274,32 @@ __device__ __forceinline__ void series_block(const GeomDev<T>* __restrict__ geom
         len = max((int64_t)0, i1 - i0) * NRED;
     }
     const gdp P = (gdp)src;
-    double acc[8];
+    if (tid < BLK) {
+        double acc[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) acc[u] = 0.0;
-    int64_t i = tid;
-    for (; i + 7 * BD < len; i += 8 * BD) {
-        double x[8];
+        for (int u = 0; u < 8; ++u) acc[u] = 0.0;
+        int64_t i = tid;
+        for (; i + 7 * BLK < len; i += 8 * BLK) {
+            double x[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) x[u] = P[i + u * BD];
+            for (int u = 0; u < 8; ++u) x[u] = P[i + u * BLK];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) acc[u] += x[u];
+            for (int u = 0; u < 8; ++u) acc[u] += x[u];
+        }
+#pragma unroll
+        for (int u = 0; u < 7; ++u)
+            if (i + u * BLK < len) acc[u] += P[i + u * BLK];
+        double v = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
+        // lanes l, l ^ 8, l ^ 16, ... hold the same sum (l % 8)
+        v += __shfl_xor(v, 8, 64);
+        v += __shfl_xor(v, 16, 64);
+        v += __shfl_xor(v, 32, 64);
+        if (lane < NRED) wsum[wv][lane] = v;
     }
-#pragma unroll
-    for (int u = 0; u < 7; ++u)
-        if (i + u * BD < len) acc[u] += P[i + u * BD];
-    double v = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
-    // lanes l, l ^ 8, l ^ 16, ... hold the same sum (l % 8)
-    v += __shfl_xor(v, 8, 64);
-    v += __shfl_xor(v, 16, 64);
-    v += __shfl_xor(v, 32, 64);
-    if (lane < NRED) wsum[wv][lane] = v;
     __syncthreads();
     if (tid < NRED) {
         double r = wsum[0][tid];
-        for (int k = 1; k < nwv; ++k) r += wsum[k][tid];
+        for (int k = 1; k < BLK / 64; ++k) r += wsum[k][tid];
         if (first) {
             chunks[c * NRED + tid] = r;
         } else if (tau <= R.ctl->tmax) {
