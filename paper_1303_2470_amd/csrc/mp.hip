@@ -2237,9 +2237,11 @@ __global__ void k_state_out(const int8_t* __restrict__ cls, const int32_t* __res
 
 // ------------------------------------------------------------------ host side
 struct TuneKey {
-    int prec;
+    int prec, uptake;
     std::vector<int64_t> shape;
-    bool operator<(const TuneKey& o) const { return std::tie(prec, shape) < std::tie(o.prec, o.shape); }
+    bool operator<(const TuneKey& o) const {
+        return std::tie(prec, uptake, shape) < std::tie(o.prec, o.uptake, o.shape);
+    }
 };
 struct TuneVal {
     int K, gsz, variant;
@@ -2651,8 +2653,10 @@ bool march_fits(const lbmp_mp* h, int G) {
 
 // ---- on-disk tuning cache: one JSON object per line,
 // {"key": "...", "variant": v, "K": k, "species_per_block": g, "ms": t}; the
-// key names the build, the precision and every geometry's shape, fluid and
-// interfacial node counts and species count; the last line with a key wins.
+// key names the build, the precision, the uptake mode (a quarter of the
+// quantities move: other plans are the fastest, and not all are legal) and every
+// geometry's shape, fluid and interfacial node counts and species count; the
+// last line with a key wins.
 // File: $LBMP_TUNE_CACHE, else $HOME/.cache/lbmp/tune.jsonl; LBMP_TUNE_CACHE
 // set to an empty string turns it off. Unreadable or unwritable files are
 // ignored (the tuner then times the candidates).
@@ -2663,7 +2667,7 @@ std::string tune_cache_path() {
 }
 
 std::string tune_key_string(const lbmp_mp* h) {
-    std::string k = "build " __DATE__ " " __TIME__ "; fp" + std::to_string(h->prec);
+    std::string k = "build " __DATE__ " " __TIME__ "; fp" + std::to_string(h->prec) + (h->uptake ? "; uptake" : "");
     for (const auto& g : h->g)
         k += "; " + std::to_string(g.flow->nx) + "x" + std::to_string(g.flow->ny) + "x" + std::to_string(g.flow->nz) +
              " nf " + std::to_string(g.nf) + " ni " + std::to_string(g.NI) + " S " + std::to_string(g.S);
@@ -2760,7 +2764,7 @@ bool tile_allowed(const lbmp_mp* h, int v, int K, int gs) {
 }
 
 TuneKey tune_key(const lbmp_mp* h) {
-    TuneKey key{h->prec, {}};
+    TuneKey key{h->prec, h->uptake, {}};
     for (const auto& g : h->g)
         key.shape.insert(key.shape.end(), {g.flow->nx, g.flow->ny, g.flow->nz, g.S, g.nf, g.NI});
     return key;
@@ -2846,7 +2850,7 @@ lbmp_status choose_tile(lbmp_mp* h, bool* chosen) {
 // Pick (K, species per block) by timing steps of each candidate on the
 // set-up tables before the state exists: a short screening run of every
 // candidate, then a longer steady-state run (warm caches and clocks) of the
-// fastest few. Results are cached per (precision, shapes) for the life of the
+// fastest few. Results are cached per (precision, mode, shapes) for the life of the
 // process and on disk (see tune_cache_path).
 lbmp_status autotune(lbmp_mp* h) {
     const int maxS = max_species(h);
