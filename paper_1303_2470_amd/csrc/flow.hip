@@ -194,6 +194,10 @@ __global__ void __launch_bounds__(256) k_bgk_step(const int32_t* __restrict__ gn
     }
 }
 
+// Maximum of d >= 0 and x >= 0; infinite once x is not finite (fmax drops a
+// NaN, and a flow that is NaN everywhere would have a residual of zero).
+__device__ __forceinline__ double fmax_finite(double d, double x) { return x < INFINITY ? fmax(d, x) : INFINITY; }
+
 // Lattices of at most BRES_NODES fluid nodes: the whole solve in one block,
 // populations in LDS (152 B a node), one node per thread, until the residual
 // falls below tol or nsteps are done. A launch per step cost 5.7 us however
@@ -267,7 +271,7 @@ __global__ void __launch_bounds__(BS) k_bgk_resident(const int32_t* __restrict__
 #pragma unroll
                 for (int k = 0; k < 3; ++k) {
                     const double a = 0.5 * (ua[k] + ub[k]), b = 0.5 * (ub[k] + uc[k]);
-                    d = fmax(d, act ? fabs(a - b) : 0.0);
+                    d = fmax_finite(d, act ? fabs(a - b) : 0.0);
                     m = fmax(m, act ? fabs(a) : 0.0);
                 }
                 for (int s = 32; s > 0; s >>= 1) {
@@ -312,8 +316,9 @@ __global__ void __launch_bounds__(BS) k_bgk_resident(const int32_t* __restrict__
     }
 }
 
-// Block maxima of |ubar(t) - ubar(t-1)| and |ubar(t)| over all components,
-// ubar(t) = (u(t) + u(t-1))/2, from the velocities of the last three steps.
+// Block maxima of |ubar(t) - ubar(t-1)| (infinite where a component is not
+// finite) and |ubar(t)| over all components, ubar(t) = (u(t) + u(t-1))/2, from
+// the velocities of the last three steps.
 __global__ void __launch_bounds__(256) k_resid(const double* __restrict__ u2, const double* __restrict__ u1,
                                                const double* __restrict__ u0, int64_t n3, double* __restrict__ part) {
     __shared__ double sd[256], sm[256];
@@ -321,7 +326,7 @@ __global__ void __launch_bounds__(256) k_resid(const double* __restrict__ u2, co
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n3;
          i += (int64_t)gridDim.x * blockDim.x) {
         const double a = 0.5 * (u0[i] + u1[i]), b = 0.5 * (u1[i] + u2[i]);
-        d = fmax(d, fabs(a - b));
+        d = fmax_finite(d, fabs(a - b));
         m = fmax(m, fabs(a));
     }
     sd[threadIdx.x] = d;
