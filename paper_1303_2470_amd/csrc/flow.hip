@@ -21,13 +21,17 @@ namespace lbmp {
 // Populations are stored in tiles of PT nodes, [tile][19][PT]: a block reads
 // and writes one stretch of memory instead of 19 (+ 19) that lie N_F values
 // apart (256^3 porous medium: 503 -> 467 us a step; tiles of 64 to 4,096 nodes
-// within 1 %). PT = 1, node by node, needs no room for a last tile that is not
+// within 1 %). PT = 0, [19][N_F], needs no room for a last tile that is not
 // full: for the resident kernel, which loads them once per launch, and for a
-// scratch that has no such room.
+// scratch that has no such room (600 steps of 349,500 nodes: 17 ms; node by
+// node, [N_F][19], 49 ms).
 constexpr int TILE = 256;
 __host__ __device__ constexpr int64_t tiled(int64_t nf) { return (nf + TILE - 1) / TILE * TILE; }
 template <int PT>
-__device__ __forceinline__ int64_t pidx(int k, int64_t i) { return (i / PT * 19 + k) * PT + i % PT; }
+__device__ __forceinline__ int64_t pidx(int k, int64_t i, int64_t NF) {
+    if constexpr (PT == 0) return k * NF + i;
+    else return (i / PT * 19 + k) * PT + i % PT;
+}
 
 struct BGKParams {
     double om, pre;  // 1 / tau, 1 - 1 / (2 tau)
@@ -107,7 +111,7 @@ __global__ void k_bgk_init(double* __restrict__ fo, int64_t NF, BGKParams P, dou
     for (int k = 0; k < NL; ++k) f[k + 1] = lw(k);
     double rho, ux, uy, uz;
     bgk_collide(f, P, rho, ux, uy, uz);
-    for (int k = 0; k < 19; ++k) fo[pidx<PT>(k, i)] = f[k];
+    for (int k = 0; k < 19; ++k) fo[pidx<PT>(k, i, NF)] = f[k];
     u0[i] = ux;
     u0[NF + i] = uy;
     u0[2 * NF + i] = uz;
@@ -145,7 +149,7 @@ __global__ void k_bgk_table(const int32_t* __restrict__ gnode, const int32_t* __
 #pragma unroll
     for (int k = 0; k < NL; ++k) {
         const int32_t j = up.at(gidx, k);
-        pull[k * NF + i] = (int32_t)(j < 0 ? pidx<TILE>((k ^ 1) + 1, i) : pidx<TILE>(k + 1, j));
+        pull[k * NF + i] = (int32_t)(j < 0 ? pidx<TILE>((k ^ 1) + 1, i, NF) : pidx<TILE>(k + 1, j, NF));
     }
 }
 
@@ -168,7 +172,7 @@ __global__ void __launch_bounds__(256) k_bgk_step(const int32_t* __restrict__ gn
     const int64_t i = blk * blockDim.x + threadIdx.x;
     if (i >= NF) return;
     double f[19];
-    f[0] = fi[pidx<PT>(0, i)];
+    f[0] = fi[pidx<PT>(0, i, NF)];
     if constexpr (TAB) {
         int32_t at[NL];
 #pragma unroll
@@ -180,13 +184,13 @@ __global__ void __launch_bounds__(256) k_bgk_step(const int32_t* __restrict__ gn
 #pragma unroll
         for (int k = 0; k < NL; ++k) {
             const int32_t j = up.at(gidx, k);
-            f[k + 1] = fi[j < 0 ? pidx<PT>((k ^ 1) + 1, i) : pidx<PT>(k + 1, (uint32_t)j)];
+            f[k + 1] = fi[j < 0 ? pidx<PT>((k ^ 1) + 1, i, NF) : pidx<PT>(k + 1, (uint32_t)j, NF)];
         }
     }
     double rho, ux, uy, uz;
     bgk_collide(f, P, rho, ux, uy, uz);
 #pragma unroll
-    for (int k = 0; k < 19; ++k) fo[pidx<PT>(k, i)] = f[k];
+    for (int k = 0; k < 19; ++k) fo[pidx<PT>(k, i, NF)] = f[k];
     if (uout) {
         uout[i] = ux;
         uout[NF + i] = uy;
@@ -231,7 +235,7 @@ __global__ void __launch_bounds__(BS) k_bgk_resident(const int32_t* __restrict__
     }
     // lanes without a node carry the state at rest along
 #pragma unroll
-    for (int k = 0; k < 19; ++k) pop[k * BS + i] = act ? F[pidx<1>(k, i)] : (k == 0 ? W_REST : lw(k - 1));
+    for (int k = 0; k < 19; ++k) pop[k * BS + i] = act ? F[pidx<0>(k, i, NF)] : (k == 0 ? W_REST : lw(k - 1));
     // velocities of the last step (slot step0 % 3) and the one before
     const int s0 = (int)(step0 % 3);
     double ua[3], ub[3], uc[3];
@@ -299,7 +303,7 @@ __global__ void __launch_bounds__(BS) k_bgk_resident(const int32_t* __restrict__
     const int s1 = (int)((step0 + done) % 3);
     if (act) {
 #pragma unroll
-        for (int k = 0; k < 19; ++k) F[pidx<1>(k, i)] = pop[k * BS + i];
+        for (int k = 0; k < 19; ++k) F[pidx<0>(k, i, NF)] = pop[k * BS + i];
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
             U[s1][d * NF + i] = ua[d];
@@ -488,7 +492,7 @@ static lbmp_status flow_solve(const lbmp_geometry* g, double tau, const double f
     if (tab) k_bgk_table<<<nbf, 256, 0, s>>>(gnode, gidx, NF, f->nx, f->ny, f->nz, pull);
     BGKParams P{1.0 / tau, 1.0 - 0.5 / tau, force[0], force[1], force[2]};
     if (tiles) k_bgk_init<TILE><<<nbf, 256, 0, s>>>(fa, NF, P, U[0]);
-    else k_bgk_init<1><<<nbf, 256, 0, s>>>(fa, NF, P, U[0]);
+    else k_bgk_init<0><<<nbf, 256, 0, s>>>(fa, NF, P, U[0]);
     // before step 2 the history holds the start only
     LBMP_HIP(hipGetLastError());
     double resv = INFINITY;
@@ -539,7 +543,7 @@ static lbmp_status flow_solve(const lbmp_geometry* g, double tau, const double f
         };
         if (tab) go(std::true_type(), std::integral_constant<int, TILE>());
         else if (tiles) go(std::false_type(), std::integral_constant<int, TILE>());
-        else go(std::false_type(), std::integral_constant<int, 1>());
+        else go(std::false_type(), std::integral_constant<int, 0>());
         std::swap(fa, fb);
         step = sn;
         if (check) {
