@@ -2833,14 +2833,34 @@ lbmp_status choose_tile(lbmp_mp* h, bool* chosen) {
             return st;
         }
     }
-    int64_t work = 0;
-    for (const auto& g : h->g) work += g.nf * g.S;
+    int64_t work = 0, nodes = 0;
+    for (const auto& g : h->g) {
+        work += g.nf * g.S;
+        nodes += g.N;
+    }
     // Launch-bound sizes, where timing candidates would cost more than any of
     // them could save: the resident kernel wherever the fields fit its blocks
-    // (0.7 against 12 us a step on a 32-node slit), else one quantity per block
-    // (12 against 21-26 us a step for variant 0 on 17 k nodes x 3 species).
+    // (0.7 against 12 us a step on a 32-node slit), else the flat kernel or
+    // variant 0 with all species in a block. The flat kernel loads every lattice
+    // node's fields and tables, variant 0 leaves blocks and lanes without a fluid
+    // node out but walks its quantities and species one after the other, so the
+    // line is the lattice's size in bytes, whatever the porosity (us a step, FP32
+    // and FP64; 15 to 80 % fluid are within 5 %):
+    //                          variant 0       9, K = 1        9, K = 4
+    //   40^3, 1 species       7.4   9.9      6.1   8.2       5.7    6.8
+    //         4 species      17.5  27.7     12.5  23.8      11.7   17.6
+    //   48^3, 1 species       7.9  10.2      7.4  12.1       7.0   10.3
+    //   60^3, 1 species      13.5  18.1     11.6  21.4      11.7   20.0
+    //   64^2 x 256, 5 % fluid, 1 species
+    //                        35.7  56.3     39.7  90.6      37.3   66.8
+    // In uptake mode variant 9 moves the one quantity that is not zero and is
+    // the faster one throughout (the same lattices: 4.7 to 30.7 us).
     if (work < (1 << 16)) {
-        v = {1, 1, tile_allowed(h, 10, 1, 1) ? 10 : 9};
+        const int64_t bytes = nodes * (h->prec / 8);
+        if (tile_allowed(h, 10, 1, 1)) v = {1, 1, 10};
+        else if (h->uptake || bytes <= (1 << 19)) v = {1, 1, 9};
+        else if (bytes <= (1 << 20)) v = {4, 1, 9};
+        else v = {1, maxS, 0};
         remember(key, v);
         return take(v);
     }
