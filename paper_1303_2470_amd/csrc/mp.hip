@@ -41,10 +41,10 @@
 #include <type_traits>
 
 #include "lbmp_internal.hpp"
+#include "plan.hpp"
 
 namespace lbmp {
 
-constexpr int BLK = 256;   // threads per block (4 waves)
 constexpr int NRED = 8;    // FP64 sums per (species, step)
 constexpr int KC = 16;     // FP64 constants per species for the DMA kernel
 constexpr int SETUP_RED = 12;
@@ -234,7 +234,6 @@ template <> __device__ __forceinline__ double store_round<double>(double v, uint
 // 4.8 us on a single slit (of 19) and 11.6 us on the batched slits.
 // Lattices with many tiles go through two stages, one launch apart: chunks of
 // RCH tile partials, then the chunk sums.
-constexpr int RCH = 2048;
 
 struct Red {
     const int32_t* work;  // (geometry, species) pairs
@@ -479,8 +478,6 @@ __global__ void __launch_bounds__(BLK) k_mp_step(const GeomDev<T>* __restrict__ 
 // (K+2) x (TY+2) x (TX+2) values, into one of two LDS buffers while it updates
 // the previous field from the other buffer. Link data stay in registers for
 // all the fields of the block.
-constexpr int TX = 64, TY = BLK / TX;
-
 template <int K>
 struct Box {
     static constexpr int PX = TX + 2, PY = TY + 2, PL = PX * PY, N = PL * (K + 2);
@@ -2315,25 +2312,8 @@ namespace {
 
 constexpr int GRAPH_CHUNK = 64;
 
-// chunks reserved per geometry: twice the count of full chunks of the
-// smaller block (256 nodes)
-int64_t gather_chunk_cap(int64_t nf) { return 2 * ((std::max<int64_t>(nf, 1) + BLK - 1) / BLK); }
-
-int64_t ntile_for(const lbmp_flow* f, int K, int variant) {
-    const int64_t zb = (f->nz + K - 1) / K;  // K = z-planes per tile (z-segment for variant 2)
-    // variant 8: up to two reduction tiles (halves) per chunk; chunks are cut
-    // shorter where their halo would not fit, up to the capacity reserved
-    if (variant == 8) return 2 * gather_chunk_cap(f->nf);
-    // variant 3: K reduction tiles (TX x TY) per block of TX x (K TY), one z-plane
-    // (variant 5: the same with full rows)
-    if (variant == 3 || variant == 5)
-        return K * (int64_t)((f->nx + TX - 1) / TX) * ((f->ny + K * TY - 1) / (K * TY)) * f->nz;
-    // variant 4 (6: full rows, 7: lane compaction): K reduction tiles (TX x TY) per block of K planes
-    if (variant == 4 || variant == 6 || variant == 7) return K * (int64_t)((f->nx + TX - 1) / TX) * ((f->ny + TY - 1) / TY) * ((f->nz + K - 1) / K);
-    if (variant == 9) return (f->N + BLK - 1) / BLK;
-    if (variant == 10) return 1;
-    if (variant >= 1) return (int64_t)((f->nx + TX - 1) / TX) * ((f->ny + TY - 1) / TY) * zb;
-    return (((int64_t)f->nx * f->ny + BLK - 1) / BLK) * zb;
+PlanGeom plan_of(const GeomHost& g) {
+    return {g.flow->nx, g.flow->ny, g.flow->nz, g.S, g.nf, g.nch, g.gnh};
 }
 
 // set-up scratch: pout 18 N | b64 3 N | src64 N | block partials | final sums |
@@ -2448,9 +2428,9 @@ lbmp_mp* make_handle(const lbmp_flow* const* flows, const lbmp_species* species,
         g.N = g.flow->N;
         g.NI = g.flow->ni;
         g.nf = g.flow->nf;
-        g.ntile_max = std::max({ntile_for(g.flow, 1, 0), ntile_for(g.flow, 1, 1), ntile_for(g.flow, 1, 3),
-                                ntile_for(g.flow, 2, 3), ntile_for(g.flow, 2, 4), ntile_for(g.flow, 4, 6),
-                                ntile_for(g.flow, 2, 8)});
+        const PlanGeom p = plan_of(g);
+        g.ntile_max = std::max({plan_tiles(p, 0, 1), plan_tiles(p, 1, 1), plan_tiles(p, 3, 1), plan_tiles(p, 3, 2),
+                                plan_tiles(p, 4, 2), plan_tiles(p, 6, 4), plan_tiles(p, 8, 2)});
     }
     return h;
 }
@@ -2596,11 +2576,11 @@ lbmp_status upload_geoms(lbmp_mp* h) {
         d.N = g.N; d.NI = std::max<int64_t>(g.NI, 1);
         d.pb = (int)(((int64_t)f->nx * f->ny + BLK - 1) / BLK);
         d.zb = (f->nz + h->K - 1) / h->K;
-        d.ngrp = h->variant >= 9 ? g.S * (nquant(h) / h->K) : (g.S + h->gsz - 1) / h->gsz;
-        d.ntile = h->variant == 8 ? g.gnh * g.nch : ntile_for(f, h->K, h->variant);
+        const PlanGeom p = plan_of(g);
+        d.ngrp = plan_groups(p, h->variant, h->K, h->gsz, nquant(h));
+        d.ntile = plan_partials(p, h->variant, h->K);
         d.blk0 = blk;
-        // variants 3-7: one block per K tiles; variant 8: one per chunk
-        blk += (h->variant == 8 ? g.nch : (h->variant >= 3 && h->variant < 8 ? d.ntile / h->K : d.ntile)) * d.ngrp;
+        blk += plan_blocks(p, h->variant, h->K, h->gsz, nquant(h));
         d.cls = f->d.cls; d.slot = f->d.slot;
         d.pin = (const T*)g.pin; d.sig = (const double*)g.sig; d.src = (const T*)g.src; d.a = (const T*)g.a;
         d.X0 = (T*)g.X0; d.X1 = (T*)g.X1; d.Xa = (T*)g.Xa;
@@ -2755,12 +2735,12 @@ bool tile_allowed(const lbmp_mp* h, int v, int K, int gs) {
                       ((v == 5 || v == 6) && K == 2 && full_rows(h)) || (v == 6 && K == 4 && full_rows(h)) ||
                       (v == 8 && K == 2 && gather)) &&
                      gs >= 1 && gs <= DMA_GMAX && h->prec == LBMP_FP32 && dma_fits(h);
-    // variant 9: blocks of 256 nodes x species x groups must stay a 32-bit count
-    bool flat = true;
-    for (const auto& g : h->g) flat = flat && (g.N + BLK - 1) / BLK * g.S * 4 <= (int64_t)INT32_MAX;
-    const bool ok9 = v == 9 && gs == 1 && flat && (h->uptake ? K == 1 : (K == 1 || K == 2 || K == 4));
+    const bool ok9 = v == 9 && gs == 1 && (h->uptake ? K == 1 : (K == 1 || K == 2 || K == 4));
     const bool ok10 = v == 10 && K == 1 && gs == 1 && max_nf(h) <= 512 * res_npt(h->prec);
-    return ok01 || ok2 || ok3 || ok9 || ok10;
+    if (!(ok01 || ok2 || ok3 || ok9 || ok10)) return false;
+    std::vector<PlanGeom> p;
+    for (const auto& g : h->g) p.push_back(plan_of(g));
+    return plan_launchable(p.data(), h->ngeom, v, K, gs, nquant(h));
 }
 
 TuneKey tune_key(const lbmp_mp* h) {
@@ -2902,10 +2882,15 @@ lbmp_status autotune(lbmp_mp* h) {
                 }
                 if (K == 2 && (gs <= maxS || gs == 2) && tile_allowed(h, 8, 2, gs)) cand.push_back({K, gs, 8});
             }
+    cand.erase(std::remove_if(cand.begin(), cand.end(),
+                              [&](const TuneVal& c) { return !tile_allowed(h, c.variant, c.K, c.gsz); }),
+               cand.end());
     hipEvent_t e0, e1;
     LBMP_HIP(hipEventCreate(&e0));
     LBMP_HIP(hipEventCreate(&e1));
-    // time `reps` steps of candidate c after `warm` untimed ones (ms per step)
+    // time `reps` steps of candidate c after `warm` untimed ones (ms per step);
+    // infinite where the runtime refuses a launch (the rest of the steps would
+    // be timed without it)
     auto time_cand = [&](const TuneVal& c, int warm, int reps, float* ms) -> lbmp_status {
         h->K = c.K;
         h->gsz = c.gsz;
@@ -2913,12 +2898,13 @@ lbmp_status autotune(lbmp_mp* h) {
         lbmp_status st = upload(h);
         if (st != LBMP_OK) return st;
         do_steps(h, warm, h->stream);
+        const bool refused = hipGetLastError() != hipSuccess;
         LBMP_HIP(hipEventRecord(e0, h->stream));
-        do_steps(h, reps, h->stream);
+        if (!refused) do_steps(h, reps, h->stream);
         LBMP_HIP(hipEventRecord(e1, h->stream));
         LBMP_HIP(hipEventSynchronize(e1));
         LBMP_HIP(hipEventElapsedTime(ms, e0, e1));
-        *ms /= (float)reps;
+        *ms = refused ? INFINITY : *ms / (float)reps;
         return LBMP_OK;
     };
     // screening: one untimed and three timed steps per candidate
@@ -2927,8 +2913,9 @@ lbmp_status autotune(lbmp_mp* h) {
         float ms = 0;
         lbmp_status st = time_cand(c, 1, 3, &ms);
         if (st != LBMP_OK) return st;
-        scored.push_back({ms, c});
+        if (std::isfinite(ms)) scored.push_back({ms, c});
     }
+    if (scored.empty()) return fail(LBMP_EINVAL, "too many nodes and species for one launch of any step kernel");
     std::stable_sort(scored.begin(), scored.end(),
                      [](const std::pair<float, TuneVal>& a, const std::pair<float, TuneVal>& b) { return a.first < b.first; });
     // steady state: the fastest four again, each after about 50 ms of untimed
