@@ -136,12 +136,25 @@ def _torch_cuda():
     return torch
 
 
-def _enter(stream, *tensors, event=None, ask=False):
+class _Events(dict):
+    """Events a handle keeps instead of creating one a call (53 -> 45 us for a
+    small predict, which waits both ways). An event belongs to the device of
+    the first stream it is recorded on and is refused by others, and the
+    current device may change between calls: one event per device."""
+
+    def of(self, stream):
+        event = self.get(stream.device_index)
+        if event is None:
+            import torch
+            event = self[stream.device_index] = torch.cuda.Event()
+        return event
+
+
+def _enter(stream, *tensors, events=None, ask=False):
     """Order work queued on `stream` after the caller's current stream (which
     produced the tensors and the workspaces' previous contents), and tell the
     caching allocator that `stream` uses the tensors; returns the current
-    stream. `event`: one kept by the handle instead of one created here (53 ->
-    45 us for a small predict, which waits both ways). ask: the current stream
+    stream. events: the handle's, None for an event of this call. ask: the current stream
     is idle as a rule between calls (training and propagation steps, whose
     results stay in the handle), and then has nothing to wait for: asking an
     idle stream takes 1 us, the event and the wait 17 (asking a busy one 8). A
@@ -149,22 +162,17 @@ def _enter(stream, *tensors, event=None, ask=False):
     import torch
     cur = torch.cuda.current_stream()
     if not ask or torch.cuda.is_current_stream_capturing() or not cur.query():
-        stream.wait_event(cur.record_event(event))
+        stream.wait_event(cur.record_event(events.of(cur) if events is not None else None))
     for t in tensors:
         if t is not None:
             t.record_stream(stream)
     return cur
 
 
-def _leave(stream, cur, event=None):
+def _leave(stream, cur, events):
     """Order the caller's current stream after the work just queued on `stream`
     (so results can be used there without an explicit synchronisation)."""
-    cur.wait_event(stream.record_event(event))
-
-
-def _event():
-    import torch
-    return torch.cuda.Event()
+    cur.wait_event(stream.record_event(events.of(stream)))
 
 
 def _ptr(a: np.ndarray):
@@ -309,7 +317,7 @@ class MP:
     def __init__(self, handle, ws, flows, n_species, stream, keep):
         self.handle, self.ws, self.flows, self.n_species, self.stream = handle, ws, flows, n_species, stream
         self._keep = keep
-        self._event = _event()
+        self._events = _Events()
 
     def step(self, n: int):
         mp_step_n(self, n)
@@ -396,7 +404,7 @@ def mp_uptake(mp: MP, geom: int = 0, t0: int = 0, count: int | None = None) -> d
 def mp_step_n(mp: MP, n: int):
     """Queue n steps on the handle's stream (asynchronous; ordered after the
     caller's current stream)."""
-    _enter(mp.stream, event=mp._event, ask=True)
+    _enter(mp.stream, events=mp._events, ask=True)
     _check(_lib.mp_step_n(mp.handle, int(n)))
 
 
@@ -477,7 +485,7 @@ class Surrogate:
         _check(_lib.sg_workspace_bytes(batch_max, ctypes.byref(nb)))
         self.ws = torch.empty(nb.value, dtype=torch.uint8, device="cuda")
         self.stream = stream or torch.cuda.Stream()
-        self._event, self._done = _event(), _event()
+        self._events, self._done = _Events(), _Events()
         _enter(self.stream, self.ws)
         self.batch_max = batch_max
         h = ctypes.c_void_p()
@@ -506,7 +514,7 @@ class Surrogate:
     def train_step(self, x, y, idx, B: int, lr: float, want_loss: bool = False):
         """x, y: torch float32 CUDA tensors (n, 6), (n,); idx: int32 CUDA tensor (>= B) or None."""
         loss = ctypes.c_float()
-        _enter(self.stream, x, y, idx, event=self._event, ask=True)
+        _enter(self.stream, x, y, idx, events=self._events, ask=True)
         _check(_lib.sg_train_step(self.handle, ctypes.c_void_p(x.data_ptr()), ctypes.c_void_p(y.data_ptr()),
                                   ctypes.c_void_p(idx.data_ptr()) if idx is not None else None, int(B),
                                   float(lr), ctypes.byref(loss) if want_loss else None))
@@ -515,7 +523,7 @@ class Surrogate:
     def gradients(self, x, y, B: int):
         g = np.zeros(self.n_params, dtype=np.float32)
         loss = ctypes.c_float()
-        _enter(self.stream, x, y, event=self._event)
+        _enter(self.stream, x, y, events=self._events)
         _check(_lib.sg_gradients(self.handle, ctypes.c_void_p(x.data_ptr()), ctypes.c_void_p(y.data_ptr()),
                                  int(B), _ptr(g), ctypes.byref(loss)))
         return g, loss.value
@@ -528,7 +536,7 @@ class Surrogate:
         n = x.shape[0]
         if out is None:
             out = torch.empty(n, dtype=torch.float32, device="cuda")
-        cur = _enter(self.stream, x, out, event=self._event)
+        cur = _enter(self.stream, x, out, events=self._events)
         _check(_lib.sg_predict(self.handle, ctypes.c_void_p(x.data_ptr()), n, ctypes.c_void_p(out.data_ptr())))
         _leave(self.stream, cur, self._done)
         return out
