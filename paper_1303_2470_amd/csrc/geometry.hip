@@ -271,3 +271,20 @@ lbmp_status build_geometry(const lbmp_geometry* g, Carver& c, FlowLayout& L, hip
 
 extern "C" const char* lbmp_last_error(void) { return lbmp::g_err; }
 extern "C" const char* lbmp_version(void) { return "lbmp 0.1 (gfx950)"; }
+
+// For the Python binding, not part of the interface (lbmp.h): whether a stream
+// is not being captured and has no work outstanding. A program may be capturing
+// some other stream meanwhile, on this thread or another; in the default mode a
+// query then fails and invalidates that capture, so it is asked in the relaxed
+// one.
+extern "C" int lbmp_stream_idle(void* hip_stream) {
+    hipStream_t s = static_cast<hipStream_t>(hip_stream);
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return 0;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;  // the null stream is never captured
+    bool idle = s == nullptr || (hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone);
+    idle = idle && hipStreamQuery(s) == hipSuccess;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (!idle) (void)hipGetLastError();  // "not ready" is no error
+    return idle ? 1 : 0;
+}

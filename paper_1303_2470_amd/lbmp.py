@@ -115,6 +115,7 @@ def load_library(path: str = LIB_PATH):
         "sg_predict": ([vp, vp, i64, vp], i32),
         "sg_sync": ([vp], i32),
         "sg_free": ([vp], None),
+        "lbmp_stream_idle": ([vp], i32),
     }
     for name, (args, res) in sig.items():
         fn = getattr(lib, name)
@@ -154,14 +155,15 @@ def _enter(stream, *tensors, events=None, ask=False):
     """Order work queued on `stream` after the caller's current stream (which
     produced the tensors and the workspaces' previous contents), and tell the
     caching allocator that `stream` uses the tensors; returns the current
-    stream. events: the handle's, None for an event of this call. ask: the current stream
-    is idle as a rule between calls (training and propagation steps, whose
-    results stay in the handle), and then has nothing to wait for: asking an
-    idle stream takes 1 us, the event and the wait 17 (asking a busy one 8). A
-    stream being captured must not be asked."""
+    stream. events: the handle's, None for an event of this call. ask: the
+    current stream is idle as a rule between calls (training and propagation
+    steps, whose results stay in the handle), and then has nothing to wait for:
+    asking an idle stream takes 1 us, the event and the wait 17 (asking a busy
+    one 8). The library asks: torch's query fails while any stream is being
+    captured, and invalidates that capture."""
     import torch
     cur = torch.cuda.current_stream()
-    if not ask or torch.cuda.is_current_stream_capturing() or not cur.query():
+    if not (ask and _lib.lbmp_stream_idle(cur.cuda_stream)):
         stream.wait_event(cur.record_event(events.of(cur) if events is not None else None))
     for t in tensors:
         if t is not None:
