@@ -386,8 +386,9 @@ __global__ void k_zero_solid_u(const uint8_t* __restrict__ solid, double* __rest
 constexpr int RES_BLOCKS = 512;
 // The pull table replaces two dependent loads and the index arithmetic by one
 // streamed load of 72 B a node: worth it while the whole solve stays in cache
-// and latency counts (131 k nodes: 9.1 us a step with it, 11.9 without), not
-// beyond (499 k nodes: 29.1 against 28.4).
+// and latency counts, not beyond. us a step with and without it, by fluid
+// nodes: 33,792 5.5 and 7.8, 103,680 8.2 and 11.0, 192,512 12.7 and 14.3,
+// 225,280 14.3 and 15.4, 252,599 (porous) 16.1 and 15.9, 357,696 21.0 and 19.3.
 constexpr int64_t TABLE_NODES = 3 << 16;
 
 // what a solve needs; room for full tiles and the pull table on top of it

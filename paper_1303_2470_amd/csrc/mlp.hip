@@ -404,8 +404,10 @@ __global__ void __launch_bounds__(512) k_train_rows(const float* __restrict__ x,
 // left to itself asks for a few and waits. 16 and 16 while the jobs leave room
 // for the registers, 4 and 8 where several waves of a SIMD hide each other's
 // loads: a training step of 512, 1,024, 1,536, 8,192 rows 25.2, 27.3, 30.3,
-// 38.6 us before, 22.6, 24.4, 26.7, 39.3 with 16 and 16, 24.0, 25.8, -, 38.6
-// with 4 and 8.
+// 38.6 us before. With 16 and 16 against 4 and 8: 512 rows 22.1 and 23.4, 1,024
+// 24.1 and 25.3, 2,048 (8 splits) 28.6 and 29.2, 4,096 (16) 32.2 and 32.2, 6,144
+// 34.4 and 34.0, 8,192 (32) 38.9 and 38.0, 16,384 60.5 and 60.5; from 32,768 rows
+// on, long splits, 2 % the other way (65,536: 203 and 208).
 constexpr int GTILES = 2 * (WIDTH / 32) * (WIDTH / 32) + 2 * (WIDTH / 32);
 
 template <int NP, int NR>

@@ -1681,13 +1681,15 @@ __device__ __forceinline__ double wave_sum(double v) {
 __device__ __forceinline__ int sum_slot(int q, int j) { return j == 0 ? (q == 0 ? 3 : q - 1) : (q == 0 ? 7 : 3 + q); }
 
 // Variant 9: one block per 256 lattice nodes, species and group of QB
-// quantities (dense fields). All 18 QB neighbour loads of a node are in
-// flight together; more blocks (QB = 1) where the lattice leaves CUs idle,
-// fewer reads of the link table (QB = 4) where it does not. nqb = 4 / QB
-// groups, or 1 in uptake mode, where only the density moves. Bound by the
-// chain of dependent loads (node class, interface slot, adsorbed value).
-// 40^3 fcc cell, 3 species, FP64 uptake: 24.5 us a step with variant 0, 10.1
-// with this.
+// quantities (dense fields). Every load of a node but its adsorbed values, which
+// need the interface slot, is in flight together; more blocks (QB = 1) where the
+// lattice leaves CUs idle, fewer reads of the link table (QB = 4) where it does
+// not. nqb = 4 / QB groups, or 1 in uptake mode, where only the density moves.
+// Small lattices are bound by launch spacing and the round trips of a step (the
+// geometry table, the loads, the adsorbed values), larger ones by the bytes of
+// the whole lattice, solid nodes included (see choose_tile). 40^3 fcc cell, 3
+// species, FP64 uptake: 24.5 us a step with variant 0, 10.1 with the class and
+// the slot waited for before the fields, 7.2 now.
 template <typename T, int QB>
 __global__ void __launch_bounds__(BLK) k_mp_flat(const GeomDev<T>* __restrict__ geoms, int ngeom, int nqb,
                                                  int64_t nblocks, const Ctl* __restrict__ ctl, Red R) {
