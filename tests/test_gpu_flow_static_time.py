@@ -1,7 +1,7 @@
 """The static flow solve at its limit, whose scratch has no room for tiled
 populations, against the solve with all the room it asks for: the same
-velocities in about the same time (both stored so that a wave's accesses are
-contiguous; 17 ms each on this lattice, where populations stored node by node
+velocities in a comparable time (both stored so that a wave's accesses are
+contiguous; 17 and 12 ms on this lattice, where populations stored node by node
 took 49)."""
 import time
 
